@@ -220,6 +220,9 @@ struct GemmParams {
     uint16_t *kc; uint16_t *vc;
     const float *rope_cos; const float *rope_sin;
     int n_q, n_kv, d, lmax_pad; int64_t kv_bstride;
+    int strip0;                             // EPI_QKV: W's first 16-row strip in the whole QKV matrix
+    float *part; int64_t part_cap;          // k-range partial sums (floats of room)
+    int full, ksplit;                       // set by launch_gemm: tiles taken whole, k-ranges of the others
 };
 void launch_gemm(const GemmParams &p, hipStream_t s);
 struct AttnPrefillParams {

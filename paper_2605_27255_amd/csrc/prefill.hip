@@ -8,8 +8,6 @@
 
 namespace pipo {
 
-__device__ __forceinline__ float silu_p(float u) { return u / (1.0f + __expf(-u)); }
-
 // ---- pair gather: X_in[m] = [E[a]; E[b]] for latent c0 + i of sequence b ----
 __global__ void k_gather_pairs(const int32_t *tokens, const uint16_t *embed, int H, int V, int pad_id,
                                PrefillGeom g, uint16_t *xin) {
@@ -210,266 +208,6 @@ void launch_rmsnorm_tiled(const float *x, const float *gain, int H, float eps, i
                           uint16_t *xl, hipStream_t s) {
     // M is a multiple of 16 (chunk rows are padded to 32 per sequence)
     hipLaunchKernelGGL(k_rmsnorm_tiled, dim3((M + 15) / 16), dim3(256), 0, s, x, gain, H, eps, M, xh, xl);
-}
-
-// ---- MFMA GEMM  C^T[N][M] = W[N][K] X[M][K]^T, both operands tiled ---------
-// Fused epilogue of one 16x16 accumulator fragment: lane (j, g) holds rows
-// 16 strip + 4 g + v of token m.  Every lane takes part in the shuffles
-// before any of them returns.
-template <int EPI>
-__device__ __forceinline__ void gemm_epi(const GemmParams &p, f32x4 val, int strip, int m) {
-    const int lane = threadIdx.x & 63, g = lane >> 4;
-    f32x4 other;
-    if (EPI == EPI_SWIGLU || EPI == EPI_QKV) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) other[v] = __shfl_xor(val[v], 32);
-    }
-    if (strip >= (p.N >> 4) || m >= p.M) return;
-    const int b = m / p.g.mpad, i = m - b * p.g.mpad;
-    if (i >= p.g.clen) return;
-    const int row0 = strip * 16 + 4 * g;
-    if (EPI == EPI_STORE) {
-        if (p.bias) val += *(const f32x4 *)(p.bias + row0);
-        *(f32x4 *)(p.out + (int64_t)m * p.N + row0) = val;
-    } else if (EPI == EPI_RESID) {
-        f32x4 *o = (f32x4 *)(p.out + (int64_t)m * p.N + row0);
-        *o = *o + val;
-    } else if (EPI == EPI_SILU) {
-        uint32_t h[4], l[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) split_bf(silu_p(val[v]), h[v], l[v]);
-        const int64_t at = tiled_index(m, row0, p.N);
-        *(u32x2 *)(p.act_hi + at) = u32x2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
-        *(u32x2 *)(p.act_lo + at) = u32x2{l[0] | (l[1] << 16), l[2] | (l[3] << 16)};
-    } else if (EPI == EPI_SWIGLU) {
-        if (g < 2) {
-            uint32_t h[4], l[4];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) split_bf(silu_p(val[v]) * other[v], h[v], l[v]);
-            const int64_t at = tiled_index(m, strip * 8 + 4 * g, p.N >> 1);
-            *(u32x2 *)(p.act_hi + at) = u32x2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
-            *(u32x2 *)(p.act_lo + at) = u32x2{l[0] | (l[1] << 16), l[2] | (l[3] << 16)};
-        }
-    } else if (EPI == EPI_QKV) {
-        const int d = p.d, hs = d >> 4;
-        const int qs = p.n_q * hs, ks = p.n_kv * hs;
-        const int pos = p.g.c0 + i;
-        if (strip < qs + ks) {
-            const bool isq = strip < qs;
-            const int sidx = isq ? strip : strip - qs;
-            const int head = sidx / hs, t = sidx - head * hs;
-            const int jr = 8 * t + 4 * (g & 1);
-            const int dim0 = (g < 2) ? jr : (d >> 1) + jr;
-            const float *cs = p.rope_cos + (int64_t)pos * (d >> 1) + jr;
-            const float *sn = p.rope_sin + (int64_t)pos * (d >> 1) + jr;
-            float r[4];
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                r[v] = (g < 2) ? val[v] * cs[v] - other[v] * sn[v] : val[v] * cs[v] + other[v] * sn[v];
-            if (isq) {   // the query as a bf16 pair hi + lo (two planes)
-                uint32_t h[4], l[4];
-#pragma unroll
-                for (int v = 0; v < 4; ++v) split_bf(r[v], h[v], l[v]);
-                const int64_t at = (((int64_t)b * p.n_q + head) * p.g.mpad + i) * d + dim0;
-                *(u32x2 *)(p.q + at) = u32x2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
-                *(u32x2 *)(p.q_lo + at) = u32x2{l[0] | (l[1] << 16), l[2] | (l[3] << 16)};
-            } else {     // the key, stored in bf16 (the cache's format)
-                u32x2 w;
-                w[0] = pack_bf2(r[0], r[1]);
-                w[1] = pack_bf2(r[2], r[3]);
-                *(u32x2 *)(p.kc + (int64_t)b * p.kv_bstride + (int64_t)head * p.lmax_pad * d +
-                           tiled_index(pos, dim0, d)) = w;
-            }
-        } else {
-            const int r0 = (strip - qs - ks) * 16 + 4 * g;
-            const int kvh = r0 / d, dim = r0 - kvh * d;
-            uint16_t *dst = p.vc + (int64_t)b * p.kv_bstride +
-                            ((int64_t)(kvh * (p.lmax_pad >> 5) + (pos >> 5)) * d + dim) * 32 + vslot(pos & 31);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) dst[v * 32] = (uint16_t)f2bf(val[v]);
-        }
-    }
-}
-
-// ---- MFMA GEMM  C^T[N][M] = W[N][K] X[M][K]^T, both operands tiled ---------
-// Workgroup tile 256 (or 320) weight rows x 64 tokens, four waves of 64 (80) x 64 (4 (5) x 4
-// fragments).  A wave's 64 weight rows are its own, so their 1 KB tiles go
-// from memory straight into its registers (one contiguous load per tile, no
-// LDS); the token tiles (X hi and lo, 16 KB per 64-wide k step) are shared by
-// the four waves through a double-buffered LDS stage.  One iteration covers
-// two 32-wide k tiles; the next iteration's weights and X are requested
-// before this one's MFMAs, and X is written to LDS after them.  MFMAs run the
-// hi plane over all 16 accumulators, then the lo plane, so dependent MFMAs
-// are 16 apart (and every accumulator sees hi, lo of one k tile before the
-// next k tile).
-// Workgroups are placed per XCD (workgroup i runs on XCD i % 8): each XCD
-// takes a contiguous run of tiles in grouped order (8 weight tiles by every
-// token tile), so the ~64 workgroups resident on one XCD cover about 8 x 8
-// tiles and share their weight and token tiles in that XCD's L2.
-constexpr int kWdToks = 64, kWdGroup = 8;   // tokens per workgroup tile; weight tiles per XCD group
-
-__device__ __forceinline__ bool wd_tile(int id, int nbn, int nbm, int &bn, int &bm) {
-    const int T = nbn * nbm;
-    const int chunk = (T + 7) / 8;
-    const int u = (id & 7) * chunk + (id >> 3);
-    if (u >= T) return false;
-    const int gsz = kWdGroup * nbm;
-    const int grp = u / gsz, r = u - grp * gsz;
-    const int first = grp * kWdGroup;
-    const int gs = min(kWdGroup, nbn - first);
-    bn = first + r % gs;
-    bm = r / gs;
-    return true;
-}
-
-template <int EPI, bool HASLO, int SW>   // SW: 16-row weight strips per wave (tile of 64 SW rows)
-__global__ __launch_bounds__(256) void k_gemm_wd(GemmParams p) {
-    constexpr int NP = HASLO ? 2 : 1;
-    constexpr int XT = NP * 2 * 4;                            // X tiles per stage: plane x k-tile x token strip
-    constexpr int XC = XT / 4;                                // 16-byte X chunks per thread per stage
-    extern __shared__ __align__(16) uint16_t lds[];           // [2][XT][512]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int j = lane & 15;
-    constexpr int ROWS = 64 * SW;
-    const int nbn = (p.N + ROWS - 1) / ROWS, nbm = (p.M + kWdToks - 1) / kWdToks;
-    int bn, bm;
-    if (!wd_tile(blockIdx.x, nbn, nbm, bn, bm)) return;
-    if (p.g.ntok) {   // a ragged batch: a token tile wholly past its sequence's last position holds only PAD rows
-        const int m0 = bm * kWdToks, sb = m0 / p.g.mpad;   // (mpad is a multiple of the tile there)
-        if (p.g.c0 + (m0 - sb * p.g.mpad) >= (p.g.ntok[sb] + p.g.tok_per_pos - 1) / p.g.tok_per_pos) return;
-    }
-    const int KT = p.K >> 5;
-    const int NI = (KT + 1) >> 1;                              // iterations of two k tiles
-    const int NS = p.N >> 4, MS = p.M >> 4;
-
-    // this wave's SW weight strips (padding strips read strip 0, masked later)
-    const uint16_t *wsrc[SW];
-#pragma unroll
-    for (int si = 0; si < SW; ++si) {
-        int strip = bn * 4 * SW + wave * SW + si;
-        strip = strip < NS ? strip : 0;
-        wsrc[si] = p.W + (int64_t)strip * KT * 512 + lane * 8;
-    }
-    // X chunks of this thread: c = tid + 256 r, tile c / 64 = (plane, kk, ms)
-    const uint16_t *xsrc[XC];
-#pragma unroll
-    for (int r = 0; r < XC; ++r) {
-        const int c = tid + 256 * r, t = c >> 6, within = c & 63;
-        const int plane = t >> 3, kk = (t >> 2) & 1, ms = t & 3;
-        int strip = bm * 4 + ms;
-        strip = strip < MS ? strip : 0;
-        xsrc[r] = (plane ? p.Xlo : p.X) + ((int64_t)strip * KT + kk) * 512 + within * 8;
-    }
-    // k tiles past the end re-read the last one (their products are skipped)
-    auto kclamp = [&](int kt) { return kt < KT ? kt : KT - 1; };
-    auto load_w = [&](int it, u32x4 (&w)[2][SW]) {
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-            for (int si = 0; si < SW; ++si)
-                w[kk][si] = *(const u32x4 *)(wsrc[si] + (int64_t)kclamp(2 * it + kk) * 512);
-    };
-    auto load_x = [&](int it, u32x4 (&x)[XC]) {
-#pragma unroll
-        for (int r = 0; r < XC; ++r) {
-            const int kk = ((tid + 256 * r) >> 8) & 1;
-            const int kt = kclamp(2 * it + kk) - kk;           // xsrc already holds the kk offset
-            x[r] = *(const u32x4 *)(xsrc[r] + (int64_t)kt * 512);
-        }
-    };
-    auto store_x = [&](int buf, const u32x4 (&x)[XC]) {
-#pragma unroll
-        for (int r = 0; r < XC; ++r) *(u32x4 *)(&lds[(buf * XT * 64 + tid + 256 * r) * 8]) = x[r];
-    };
-
-    f32x4 acc[SW][4];
-#pragma unroll
-    for (int a = 0; a < SW; ++a)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[a][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    auto mma = [&](int buf, int it, const u32x4 (&w)[2][SW]) {
-        const uint16_t *L = lds + buf * XT * 512;
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-            if (kk == 1 && 2 * it + 1 >= KT) break;            // odd K: no second tile
-            u32x4 bh[4], bl[4];
-#pragma unroll
-            for (int mi = 0; mi < 4; ++mi) {
-                bh[mi] = *(const u32x4 *)(&L[((0 * 2 + kk) * 4 + mi) * 512 + lane * 8]);
-                if (HASLO) bl[mi] = *(const u32x4 *)(&L[((1 * 2 + kk) * 4 + mi) * 512 + lane * 8]);
-            }
-#pragma unroll
-            for (int si = 0; si < SW; ++si)
-#pragma unroll
-                for (int mi = 0; mi < 4; ++mi) acc[si][mi] = mfma16(w[kk][si], bh[mi], acc[si][mi]);
-            if (HASLO) {
-#pragma unroll
-                for (int si = 0; si < SW; ++si)
-#pragma unroll
-                    for (int mi = 0; mi < 4; ++mi) acc[si][mi] = mfma16(w[kk][si], bl[mi], acc[si][mi]);
-            }
-        }
-    };
-
-    u32x4 wa[2][SW], wb[2][SW], xr[XC];
-    load_x(0, xr);
-    load_w(0, wa);
-    store_x(0, xr);
-    __syncthreads();
-    // iteration it: request it + 1, multiply it, stage X of it + 1
-    for (int it = 0; it < NI; it += 2) {
-        load_x(it + 1, xr);
-        load_w(it + 1, wb);
-        mma(0, it, wa);
-        store_x(1, xr);
-        __syncthreads();
-        if (it + 1 >= NI) break;
-        load_x(it + 2, xr);
-        load_w(it + 2, wa);
-        mma(1, it + 1, wb);
-        store_x(0, xr);
-        __syncthreads();
-    }
-
-#pragma unroll
-    for (int si = 0; si < SW; ++si)
-#pragma unroll
-        for (int mi = 0; mi < 4; ++mi)
-            gemm_epi<EPI>(p, acc[si][mi], bn * 4 * SW + wave * SW + si, bm * kWdToks + mi * 16 + j);
-}
-
-// Tile height: 256 or 320 weight rows, whichever gives the busiest compute
-// unit the fewest rows (workgroups are spread evenly over the 256 CUs, so a
-// CU runs ceil(tiles / 256) of them): at N = 2560 the 256-row tile leaves
-// 2.5 workgroups per CU (half the CUs run three), the 320-row tile two.
-template <int EPI, bool HASLO>
-static void launch_gemm_wd(const GemmParams &p, hipStream_t s) {
-    const int nbm = (p.M + kWdToks - 1) / kWdToks;
-    auto load = [&](int rows) {
-        const int tiles = ((p.N + rows - 1) / rows) * nbm;
-        return (int64_t)((tiles + 255) / 256) * rows;
-    };
-    const bool five = p.N % 320 == 0 && load(320) < load(256);
-    const int nbn = five ? p.N / 320 : (p.N + 255) / 256;
-    const int grid = 8 * ((nbn * nbm + 7) / 8);
-    const size_t lds = 2 * (HASLO ? 16 : 8) * 1024;
-    if (five) hipLaunchKernelGGL((k_gemm_wd<EPI, HASLO, 5>), dim3(grid), dim3(256), lds, s, p);
-    else hipLaunchKernelGGL((k_gemm_wd<EPI, HASLO, 4>), dim3(grid), dim3(256), lds, s, p);
-}
-
-void launch_gemm(const GemmParams &p, hipStream_t s) {
-    if (!p.Xlo) {   // the gathered embedding pairs are exact in bf16
-        if (p.epi == EPI_SILU) launch_gemm_wd<EPI_SILU, false>(p, s);
-        else launch_gemm_wd<EPI_STORE, false>(p, s);
-        return;
-    }
-    switch (p.epi) {
-        case EPI_STORE: launch_gemm_wd<EPI_STORE, true>(p, s); break;
-        case EPI_RESID: launch_gemm_wd<EPI_RESID, true>(p, s); break;
-        case EPI_SWIGLU: launch_gemm_wd<EPI_SWIGLU, true>(p, s); break;
-        default: launch_gemm_wd<EPI_QKV, true>(p, s); break;
-    }
 }
 
 // ---- causal grouped-query flash attention for a chunk of queries ----------

@@ -82,6 +82,7 @@ struct pipo_ctx {
     // prefill activations
     uint16_t *p_xin, *p_xn, *p_xn_lo, *p_q, *p_q_lo, *p_o, *p_o_lo, *p_act, *p_act_lo;
     float *p_x;
+    float *p_part; int64_t p_part_cap;   // prefill GEMM k-range partial sums
 
     uint64_t *h_seeds = nullptr;     // pinned staging for sampler seeds
     hipEvent_t seeds_done = nullptr;
@@ -369,6 +370,10 @@ extern "C" int pipo_init_weights(const pipo_config *cfg, uint64_t seed, void *st
         c->p_o_lo = a.take<uint16_t>(mcap * c->qdim);
         c->p_act = a.take<uint16_t>(mcap * F);
         c->p_act_lo = a.take<uint16_t>(mcap * F);
+        // two rounds of 256 x 128 tiles over the CUs, or 16 ranges of the widest output if that is less
+        c->p_part_cap = std::min<int64_t>((int64_t)16 << 20, 16 * round_up(mcap, 128) *
+                                          round_up(std::max<int64_t>(2 * F, c->nqkv), 256));
+        c->p_part = a.take<float>(c->p_part_cap);
         if (pass == 0) {
             if (hipMalloc(&c->amem, a.used) != hipSuccess) {
                 hipFree(c->wmem);
@@ -740,7 +745,7 @@ static int prefill_backbone(pipo_ctx *c, int32_t batch, const int32_t *d_tokens,
         GemmParams gp{};
         gp.g = g; gp.M = M;
         gp.n_q = c->nq; gp.n_kv = c->nkv; gp.d = c->d; gp.lmax_pad = c->lmax_pad; gp.kv_bstride = c->kv_bstride;
-        gp.rope_cos = c->rope_cos; gp.rope_sin = c->rope_sin;
+        gp.rope_cos = c->rope_cos; gp.rope_sin = c->rope_sin; gp.part = c->p_part; gp.part_cap = c->p_part_cap;
         GemmParams p = gp;
         if (regular) {
             PROF(PIPO_K_PREFILL_MISC);
