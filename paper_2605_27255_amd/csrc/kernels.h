@@ -197,6 +197,10 @@ struct PrefillGeom {
 };
 // Prompt tokens of sequence b.
 __device__ __forceinline__ int seq_tokens(const PrefillGeom &g, int b) { return g.ntok ? g.ntok[b] : g.n_tok; }
+// ... and its prompt's positions.
+__device__ __forceinline__ int seq_positions(const PrefillGeom &g, int b) {
+    return (seq_tokens(g, b) + g.tok_per_pos - 1) / g.tok_per_pos;
+}
 void launch_gather_pairs(const int32_t *tokens, const uint16_t *embed, int H, int V, int pad_id,
                          const PrefillGeom &g, uint16_t *xin, hipStream_t s);
 void launch_gather_pair_sum(const int32_t *tokens, const uint16_t *embed, int H, int V, int pad_id,

@@ -2,7 +2,7 @@
 // positions of every sequence.  Activations that feed an MFMA GEMM are kept
 // in the 16x32 tiled bf16 layout, as two planes hi and lo (x ~= hi + lo,
 // about 16 significant bits), so that both GEMM operands move as contiguous
-// 1 KB tiles (weights straight into registers, activations through LDS).
+// 1 KB tiles straight into LDS.
 #include "device_common.h"
 #include "kernels.h"
 
@@ -156,33 +156,29 @@ void launch_gather_tokens(const int32_t *tokens, const uint16_t *embed, int H, i
 }
 
 // ---- RMSNorm of fp32 rows into the tiled bf16 layout ----------------------
-// One workgroup per 16-row tile row: wave w first forms the sums of squares
-// of rows 4w..4w+3 (the four rows' loads interleaved), then writes every
-// fourth 16x32 tile whole: lane l normalises row l mod 16, columns
+// One workgroup of sixteen waves per 16-row tile row: wave w first forms the
+// sum of squares of row w (five 1 KB loads in flight), then writes every
+// sixteenth 16x32 tile whole: lane l normalises row l mod 16, columns
 // 8 (l / 16) .. + 7 of the tile, so each store instruction covers one
 // contiguous 1 KB tile (full cache lines, no partial-line writes shared with
-// other workgroups).
-__global__ __launch_bounds__(256) void k_rmsnorm_tiled(const float *x, const float *gain, int H, float eps,
-                                                       int M, uint16_t *xh, uint16_t *xl) {
+// other workgroups).  A small prompt has few tile rows, so the row's latency
+// is what counts there.
+__global__ __launch_bounds__(1024) void k_rmsnorm_tiled(const float *x, const float *gain, int H, float eps,
+                                                        int M, uint16_t *xh, uint16_t *xl) {
     __shared__ float s_sc[16];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r0 = blockIdx.x * 16;
     if (r0 >= M) return;
     {
-        const float *xr = x + (int64_t)(r0 + 4 * wave) * H;
-        float a[4] = {0.f, 0.f, 0.f, 0.f};
+        const float *xr = x + (int64_t)(r0 + wave) * H;
+        float a = 0.f;
+#pragma unroll 5
         for (int k = lane * 4; k < H; k += 256) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float4 v = *(const float4 *)(xr + (int64_t)q * H + k);
-                a[q] += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-            }
+            const float4 v = *(const float4 *)(xr + k);
+            a += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
         }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float t = wave_sum(a[q]);
-            if (lane == 0) s_sc[4 * wave + q] = rsqrtf(t / (float)H + eps);
-        }
+        a = wave_sum(a);
+        if (lane == 0) s_sc[wave] = rsqrtf(a / (float)H + eps);
     }
     __syncthreads();
     const int j = lane & 15, c = lane >> 4;
@@ -191,7 +187,8 @@ __global__ __launch_bounds__(256) void k_rmsnorm_tiled(const float *x, const flo
     const int KT = H >> 5;
     uint16_t *th = xh + (int64_t)(r0 >> 4) * KT * 512 + lane * 8;
     uint16_t *tl = xl + (int64_t)(r0 >> 4) * KT * 512 + lane * 8;
-    for (int kt = wave; kt < KT; kt += 4) {
+#pragma unroll 2
+    for (int kt = wave; kt < KT; kt += 16) {
         const int k = kt * 32 + c * 8;
         const float4 x0 = *(const float4 *)(xr + k), x1 = *(const float4 *)(xr + k + 4);
         const float4 g0 = *(const float4 *)(gain + k), g1 = *(const float4 *)(gain + k + 4);
@@ -207,7 +204,7 @@ __global__ __launch_bounds__(256) void k_rmsnorm_tiled(const float *x, const flo
 void launch_rmsnorm_tiled(const float *x, const float *gain, int H, float eps, int M, uint16_t *xh,
                           uint16_t *xl, hipStream_t s) {
     // M is a multiple of 16 (chunk rows are padded to 32 per sequence)
-    hipLaunchKernelGGL(k_rmsnorm_tiled, dim3((M + 15) / 16), dim3(256), 0, s, x, gain, H, eps, M, xh, xl);
+    hipLaunchKernelGGL(k_rmsnorm_tiled, dim3((M + 15) / 16), dim3(1024), 0, s, x, gain, H, eps, M, xh, xl);
 }
 
 // ---- causal grouped-query flash attention for a chunk of queries ----------
@@ -276,7 +273,7 @@ __global__ __launch_bounds__(512, 1) void k_attn_prefill(AttnPrefillParams p) {
     const float scale = 1.4426950408889634f / sqrtf((float)D);
     // a ragged batch: a block wholly past this sequence's last position holds
     // only PAD rows, whose outputs nothing reads
-    if (p.g.ntok && qpos0 >= (p.g.ntok[b] + p.g.tok_per_pos - 1) / p.g.tok_per_pos) return;
+    if (p.g.ntok && qpos0 >= seq_positions(p.g, b)) return;
 
     u32x4 qb[2][NC];   // the query rows in fp16
 #pragma unroll

@@ -24,7 +24,10 @@ __device__ __forceinline__ void gemm_epi(const GemmParams &p, f32x4 a, f32x4 c, 
     const int h = (threadIdx.x >> 5) & 1;
     if (strip >= (p.N >> 4) || m >= p.M) return;
     const int b = m / p.g.mpad, i = m - b * p.g.mpad;
-    if (i >= p.g.clen) return;
+    // Rows past the chunk or past a ragged batch's shorter prompt hold nothing:
+    // their X may be stale (a tile of another shape was skipped there), and the
+    // cache keeps finite values at positions no prompt has reached.
+    if (i >= p.g.clen || (p.g.ntok && p.g.c0 + i >= seq_positions(p.g, b))) return;
     const int row0 = strip * 16 + 4 * h;
     if (EPI == EPI_STORE) {
         if (p.bias) {
@@ -148,7 +151,7 @@ __device__ __forceinline__ bool pad_rows(const GemmParams &p, int m0, int m1) {
     bool any = false;
     for (int sb = m0 / p.g.mpad; sb * p.g.mpad < m1; ++sb) {
         const int i0 = max(m0 - sb * p.g.mpad, 0);
-        any = any || p.g.c0 + i0 < (p.g.ntok[sb] + p.g.tok_per_pos - 1) / p.g.tok_per_pos;
+        any = any || p.g.c0 + i0 < seq_positions(p.g, sb);
     }
     return !any;
 }

@@ -735,6 +735,13 @@ static int prefill_backbone(pipo_ctx *c, int32_t batch, const int32_t *d_tokens,
         HIP_TRY(c, hipEventRecord(c->seeds_done, s));
     }
     const int H = c->H, F = c->F;
+    // Layers [0, L_rows) run over every position.  Of the last layer only the
+    // keys and values are needed before the last position, so the chunks
+    // compute those alone and the layer itself runs once, at the last
+    // positions (the MTP layer reads the backbone's output at every position:
+    // then every backbone layer runs over them, and the MTP layer is the last).
+    const bool mtp_layer = !regular && (c->heads & PIPO_HEADS_MTP_LAYER);
+    const int L_rows = c->L - (mtp_layer || c->L == 0 ? 0 : 1);
     PrefillGeom g{};
     for (int c0 = 0; c0 < positions; c0 += c->chunk) {
         g.B = batch; g.c0 = c0; g.clen = std::min(c->chunk, positions - c0);
@@ -763,14 +770,26 @@ static int prefill_backbone(pipo_ctx *c, int32_t batch, const int32_t *d_tokens,
             p.W = c->w_comp; p.X = c->p_xin; p.N = H; p.K = 2 * H; p.epi = EPI_STORE; p.out = c->p_x; p.bias = c->b_comp;
             { PROF(PIPO_K_PREFILL_GEMM); launch_gemm(p, s); }
         }
+        // RMSNorm, then the queries, keys and values of a layer over the chunk (`kv_only`: W's key and value rows
+        // alone, into the cache)
+        auto layer_qkv = [&](const LayerW &lw, float *xr, uint16_t *kc, uint16_t *vc, bool kv_only) {
+            { PROF(PIPO_K_PREFILL_MISC); launch_rmsnorm_tiled(xr, lw.g_attn, H, c->cfg.rms_eps, M, c->p_xn, c->p_xn_lo, s); }
+            p = gp;
+            p.strip0 = kv_only ? c->qdim >> 4 : 0;
+            p.W = lw.wqkv + (int64_t)p.strip0 * 16 * H; p.N = c->nqkv - p.strip0 * 16;
+            p.X = c->p_xn; p.Xlo = c->p_xn_lo; p.K = H; p.epi = EPI_QKV; p.q = c->p_q; p.q_lo = c->p_q_lo; p.kc = kc; p.vc = vc;
+            { PROF(PIPO_K_PREFILL_GEMM); launch_gemm(p, s); }
+        };
         for (int l = 0; l < c->L; ++l) {
             const LayerW &lw = c->layers[l];
             uint16_t *kc = c->kc + (int64_t)l * c->Bmax * c->kv_bstride;
             uint16_t *vc = c->vc + (int64_t)l * c->Bmax * c->kv_bstride;
-            { PROF(PIPO_K_PREFILL_MISC); launch_rmsnorm_tiled(c->p_x, lw.g_attn, H, c->cfg.rms_eps, M, c->p_xn, c->p_xn_lo, s); }
-            p = gp;
-            p.W = lw.wqkv; p.X = c->p_xn; p.Xlo = c->p_xn_lo; p.N = c->nqkv; p.K = H; p.epi = EPI_QKV; p.q = c->p_q; p.q_lo = c->p_q_lo; p.kc = kc; p.vc = vc;
-            { PROF(PIPO_K_PREFILL_GEMM); launch_gemm(p, s); }
+            if (l == L_rows) {   // the last layer's keys and values; its input at the last positions
+                { PROF(PIPO_K_PREFILL_MISC); launch_pick_last(c->p_x, H, g, c->x, c->ss_x, c->pos, c->step, regular, s); }
+                layer_qkv(lw, c->p_x, kc, vc, true);
+                break;
+            }
+            layer_qkv(lw, c->p_x, kc, vc, false);
             AttnPrefillParams ap{};
             ap.q = c->p_q; ap.q_lo = c->p_q_lo; ap.kc = kc; ap.vc = vc; ap.kv_bstride = c->kv_bstride; ap.g = g;
             ap.n_q = c->nq; ap.n_kv = c->nkv; ap.d = c->d; ap.lmax_pad = c->lmax_pad; ap.out_hi = c->p_o; ap.out_lo = c->p_o_lo;
@@ -787,9 +806,13 @@ static int prefill_backbone(pipo_ctx *c, int32_t batch, const int32_t *d_tokens,
             { PROF(PIPO_K_PREFILL_GEMM); launch_gemm(p, s); }
         }
         // sequences whose last position is in this chunk take it as their step state
-        { PROF(PIPO_K_PREFILL_MISC); launch_pick_last(c->p_x, H, g, c->x, c->ss_x, c->pos, c->step, regular, s); }
-        if (!regular && (c->heads & PIPO_HEADS_MTP_LAYER)) {
-            // App. B.2 over the chunk's latents (their K/V fill the MTP cache);
+        if (L_rows == c->L) {
+            PROF(PIPO_K_PREFILL_MISC);
+            launch_pick_last(c->p_x, H, g, c->x, c->ss_x, c->pos, c->step, regular, s);
+        }
+        if (mtp_layer) {
+            // App. B.2 over the chunk's latents (their K/V fill the MTP cache; the
+            // layer's output is needed at the last position only, where the heads run it);
             // the MTP stream lives in p_xin, free once the compressor has run
             float *xm = (float *)c->p_xin;
             { PROF(PIPO_K_PREFILL_MISC);
@@ -798,28 +821,12 @@ static int prefill_backbone(pipo_ctx *c, int32_t batch, const int32_t *d_tokens,
             p = gp;
             p.W = c->w_fc; p.X = c->p_act; p.Xlo = c->p_act_lo; p.N = H; p.K = 2 * H; p.epi = EPI_STORE; p.out = xm;
             { PROF(PIPO_K_PREFILL_GEMM); launch_gemm(p, s); }
-            const LayerW &lw = c->mtp;
-            { PROF(PIPO_K_PREFILL_MISC); launch_rmsnorm_tiled(xm, lw.g_attn, H, c->cfg.rms_eps, M, c->p_xn, c->p_xn_lo, s); }
-            p = gp;
-            p.W = lw.wqkv; p.X = c->p_xn; p.Xlo = c->p_xn_lo; p.N = c->nqkv; p.K = H; p.epi = EPI_QKV; p.q = c->p_q; p.q_lo = c->p_q_lo;
-            p.kc = c->kc_mtp; p.vc = c->vc_mtp;
-            { PROF(PIPO_K_PREFILL_GEMM); launch_gemm(p, s); }
-            AttnPrefillParams ap{};
-            ap.q = c->p_q; ap.q_lo = c->p_q_lo; ap.kc = c->kc_mtp; ap.vc = c->vc_mtp; ap.kv_bstride = c->kv_bstride; ap.g = g;
-            ap.n_q = c->nq; ap.n_kv = c->nkv; ap.d = c->d; ap.lmax_pad = c->lmax_pad; ap.out_hi = c->p_o; ap.out_lo = c->p_o_lo;
-            { PROF(PIPO_K_PREFILL_ATTN); launch_attn_prefill(ap, s); }
-            p = gp;
-            p.W = lw.wo; p.X = c->p_o; p.Xlo = c->p_o_lo; p.N = H; p.K = c->qdim; p.epi = EPI_RESID; p.out = xm;
-            { PROF(PIPO_K_PREFILL_GEMM); launch_gemm(p, s); }
-            { PROF(PIPO_K_PREFILL_MISC); launch_rmsnorm_tiled(xm, lw.g_ffn, H, c->cfg.rms_eps, M, c->p_xn, c->p_xn_lo, s); }
-            p = gp;
-            p.W = lw.wgu; p.X = c->p_xn; p.Xlo = c->p_xn_lo; p.N = 2 * F; p.K = H; p.epi = EPI_SWIGLU; p.act_hi = c->p_act; p.act_lo = c->p_act_lo;
-            { PROF(PIPO_K_PREFILL_GEMM); launch_gemm(p, s); }
-            p = gp;
-            p.W = lw.wdown; p.X = c->p_act; p.Xlo = c->p_act_lo; p.N = H; p.K = F; p.epi = EPI_RESID; p.out = xm;
-            { PROF(PIPO_K_PREFILL_GEMM); launch_gemm(p, s); }
+            layer_qkv(c->mtp, xm, c->kc_mtp, c->vc_mtp, true);
         }
     }
+    if (L_rows < c->L)   // the last layer at the last positions, as a decode step runs it (its key and value land again)
+        enqueue_layer(c, c->layers[L_rows], c->kc + (int64_t)L_rows * c->Bmax * c->kv_bstride,
+                      c->vc + (int64_t)L_rows * c->Bmax * c->kv_bstride, c->x, c->ss_x, s);
     c->len = positions;
     return PIPO_OK;
 }
