@@ -23,6 +23,20 @@
 
 namespace pipo {
 
+// Output element (row b, column c), as the next kernel takes it.
+__device__ __forceinline__ void put_out(const AttnDecodeParams &p, int b, int c, int D, float v) {
+    const int qd = p.n_q * D;
+    if (p.out_hi) {
+        uint32_t hi, lo;
+        split_bf(v, hi, lo);
+        const int64_t at = tiled_index(b, c, qd);
+        p.out_hi[at] = (uint16_t)hi;
+        p.out_lo[at] = (uint16_t)lo;
+    } else {
+        p.out[(int64_t)b * qd + c] = v;
+    }
+}
+
 // The merge of one (sequence, KV group) by one wave: the records of its qpg
 // heads and S splits ([qpg][S] in the partial buffer).  16 lanes take a head,
 // D / 16 dimensions each, four heads at a time; the splits go in split order,
@@ -72,11 +86,16 @@ __device__ void xl_merge(const AttnDecodeParams &p, int b, int kvh, int qpg, int
         }
         if (hj < qpg) {
             const float inv = 1.0f / L;
-            float *o = p.out + ((int64_t)b * p.n_q + kvh * qpg + hj) * D + d0;
+            if (p.out_hi) {
 #pragma unroll
-            for (int k = 0; k < DPL / 4; ++k)
-                *(float4 *)(o + 4 * k) = make_float4(acc[4 * k] * inv, acc[4 * k + 1] * inv, acc[4 * k + 2] * inv,
-                                                     acc[4 * k + 3] * inv);
+                for (int k = 0; k < DPL; ++k) put_out(p, b, (kvh * qpg + hj) * D + d0 + k, D, acc[k] * inv);
+            } else {
+                float *o = p.out + ((int64_t)b * p.n_q + kvh * qpg + hj) * D + d0;
+#pragma unroll
+                for (int k = 0; k < DPL / 4; ++k)
+                    *(float4 *)(o + 4 * k) = make_float4(acc[4 * k] * inv, acc[4 * k + 1] * inv, acc[4 * k + 2] * inv,
+                                                         acc[4 * k + 3] * inv);
+            }
         }
     }
 }
@@ -443,7 +462,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attn_decode(AttnDecodeParams p) 
                 L += ww * red[w][hj][D + 1];
                 acc += ww * red[w][hj][dim];
             }
-            p.out[((int64_t)b * p.n_q + kvh * qpg + hj) * D + dim] = acc * (1.0f / L);
+            put_out(p, b, (kvh * qpg + hj) * D + dim, D, acc * (1.0f / L));
         }
     }
 }
@@ -479,7 +498,8 @@ __global__ __launch_bounds__(D) void k_attn_merge(AttnDecodeParams p) {
     float acc = 0.f;
 #pragma unroll
     for (int sp = 0; sp < SMAX; ++sp) acc += sp < S ? s_w[sp] * ov[sp] : 0.f;
-    p.out[(int64_t)bh * D + t] = acc * s_inv;
+    const int b = bh / p.n_q;
+    put_out(p, b, (bh - b * p.n_q) * D + t, D, acc * s_inv);
 }
 
 __global__ __launch_bounds__(64) void k_xcd_probe(int *out) {

@@ -1176,12 +1176,17 @@ static void launch_u(const GemvParams &p, hipStream_t s) {
     else launch_t<NBT, KS, PRO, EPI, 4>(p, s);
 }
 
+// (decoder layers take the tiled GEMM from kTiledMinBatch sequences on: no
+// QKV or SwiGLU kernels for four column tiles)
 template <int KS, int PRO, int EPI>
-static void launch_nbt(const GemvParams &p, hipStream_t s) {
+static int launch_nbt(const GemvParams &p, hipStream_t s) {
+    constexpr bool layer = EPI == EPI_QKV || EPI == EPI_SWIGLU;
     if (p.B <= 16) launch_u<1, KS, PRO, EPI>(p, s);
     else if (p.B <= 32) launch_u<2, KS, PRO, EPI>(p, s);
     else if (p.B <= 48) launch_u<3, KS, PRO, EPI>(p, s);
-    else launch_u<4, KS, PRO, EPI>(p, s);
+    else if constexpr (!layer) launch_u<4, KS, PRO, EPI>(p, s);
+    else return -1;
+    return 0;
 }
 
 int gemv_num_groups(int N) { return N >> 4; }
@@ -1191,17 +1196,16 @@ int gemv_num_groups(int N) { return N >> 4; }
 // head (151936 rows) splits K in four, every other matrix in eight.  Any
 // other pair launches nothing and returns -1.
 int launch_gemv(const GemvParams &p, int pro, int epi, hipStream_t s) {
-    if (pro == PRO_PAIR && epi == EPI_STORE) launch_nbt<8, PRO_PAIR, EPI_STORE>(p, s);
-    else if (pro == PRO_NORM && epi == EPI_QKV) launch_nbt<8, PRO_NORM, EPI_QKV>(p, s);
-    else if (pro == PRO_F32 && epi == EPI_RESID) launch_nbt<8, PRO_F32, EPI_RESID>(p, s);
-    else if (pro == PRO_NORM && epi == EPI_SWIGLU) launch_nbt<8, PRO_NORM, EPI_SWIGLU>(p, s);
-    else if (pro == PRO_NORM && epi == EPI_LOGITS) launch_nbt<4, PRO_NORM, EPI_LOGITS>(p, s);
-    else if (pro == PRO_MTP && epi == EPI_STORE) launch_nbt<8, PRO_MTP, EPI_STORE>(p, s);
-    else if (pro == PRO_NORM && epi == EPI_STORE) launch_nbt<8, PRO_NORM, EPI_STORE>(p, s);
-    else if (pro == PRO_PAIR && epi == EPI_SILU) launch_nbt<8, PRO_PAIR, EPI_SILU>(p, s);
-    else if (pro == PRO_CAT && epi == EPI_SILU) launch_nbt<8, PRO_CAT, EPI_SILU>(p, s);
-    else return -1;
-    return 0;
+    if (pro == PRO_PAIR && epi == EPI_STORE) return launch_nbt<8, PRO_PAIR, EPI_STORE>(p, s);
+    if (pro == PRO_NORM && epi == EPI_QKV) return launch_nbt<8, PRO_NORM, EPI_QKV>(p, s);
+    if (pro == PRO_F32 && epi == EPI_RESID) return launch_nbt<8, PRO_F32, EPI_RESID>(p, s);
+    if (pro == PRO_NORM && epi == EPI_SWIGLU) return launch_nbt<8, PRO_NORM, EPI_SWIGLU>(p, s);
+    if (pro == PRO_NORM && epi == EPI_LOGITS) return launch_nbt<4, PRO_NORM, EPI_LOGITS>(p, s);
+    if (pro == PRO_MTP && epi == EPI_STORE) return launch_nbt<8, PRO_MTP, EPI_STORE>(p, s);
+    if (pro == PRO_NORM && epi == EPI_STORE) return launch_nbt<8, PRO_NORM, EPI_STORE>(p, s);
+    if (pro == PRO_PAIR && epi == EPI_SILU) return launch_nbt<8, PRO_PAIR, EPI_SILU>(p, s);
+    if (pro == PRO_CAT && epi == EPI_SILU) return launch_nbt<8, PRO_CAT, EPI_SILU>(p, s);
+    return -1;
 }
 
 }  // namespace pipo

@@ -96,7 +96,8 @@ struct AttnDecodeParams {
     const int32_t *pos;         // [B]: attend to keys 0..pos[b]
     int B, n_q, n_kv, d, lmax_pad, splits;
     float *part;                // [B][n_q][splits][attn_part_stride(d)]: o[d], m, l, padding
-    float *out;                 // fp32 [B][n_q * d]
+    float *out;                 // fp32 [B][n_q * d], or with out_hi:
+    uint16_t *out_hi, *out_lo;  // tiled [B][n_q * d] hi and lo planes (the next GEMM's X)
     // not NULL: the splits of one (sequence, KV group) run on one XCD (the
     // grid is laid out for workgroup i to run on XCD i mod 8) and the last
     // one to finish merges them through that XCD's L2; one counter per
@@ -210,6 +211,7 @@ void launch_mtp_rows(const float *xb, const int32_t *tokens, const uint16_t *emb
                      hipStream_t s);
 void launch_gather_tokens(const int32_t *tokens, const uint16_t *embed, int H, int V, int pad_id,
                           const PrefillGeom &g, float *x, hipStream_t s);
+// x holds M rows; the 16-row tiles' rows past them repeat the last one.
 void launch_rmsnorm_tiled(const float *x, const float *gain, int H, float eps, int M,
                           uint16_t *xn_hi, uint16_t *xn_lo, hipStream_t s);
 // Activations of the prefill GEMMs are a pair of tiled bf16 planes, hi and lo
@@ -224,6 +226,15 @@ struct GemmParams {
     uint16_t *kc; uint16_t *vc;
     const float *rope_cos; const float *rope_sin;
     int n_q, n_kv, d, lmax_pad; int64_t kv_bstride;
+    // A decode step's GEMM (dpos not NULL): row m is sequence m at position dpos[m],
+    // rows [rows, M) are padding.  EPI_QKV writes the query as fp32 [rows][n_q][d] to qf.
+    // EPI_RESID also writes the sum-of-squares part of every 16-row strip to ss_out and, with
+    // xn_hi, the new residual times `gain` (the next RMSNorm's) as the planes the next GEMM reads;
+    // that GEMM (EPI_QKV, EPI_SWIGLU) takes the parts [rows][nss] in ss_in and applies
+    // rsqrt(sum / K + eps) to its sums (ss_in NULL: X is normalised already)
+    const int32_t *dpos; int rows; float *qf, *ss_out;
+    const float *gain; uint16_t *xn_hi, *xn_lo;
+    const float *ss_in; int nss; float eps;
     int strip0;                             // EPI_QKV: W's first 16-row strip in the whole QKV matrix
     float *part; int64_t part_cap;          // k-range partial sums (floats of room)
     int full, ksplit;                       // set by launch_gemm: tiles taken whole, k-ranges of the others

@@ -170,7 +170,7 @@ __global__ __launch_bounds__(1024) void k_rmsnorm_tiled(const float *x, const fl
     const int r0 = blockIdx.x * 16;
     if (r0 >= M) return;
     {
-        const float *xr = x + (int64_t)(r0 + wave) * H;
+        const float *xr = x + (int64_t)min(r0 + wave, M - 1) * H;
         float a = 0.f;
 #pragma unroll 5
         for (int k = lane * 4; k < H; k += 256) {
@@ -183,7 +183,7 @@ __global__ __launch_bounds__(1024) void k_rmsnorm_tiled(const float *x, const fl
     __syncthreads();
     const int j = lane & 15, c = lane >> 4;
     const float sc = s_sc[j];
-    const float *xr = x + (int64_t)(r0 + j) * H;
+    const float *xr = x + (int64_t)min(r0 + j, M - 1) * H;
     const int KT = H >> 5;
     uint16_t *th = xh + (int64_t)(r0 >> 4) * KT * 512 + lane * 8;
     uint16_t *tl = xl + (int64_t)(r0 >> 4) * KT * 512 + lane * 8;
@@ -203,7 +203,6 @@ __global__ __launch_bounds__(1024) void k_rmsnorm_tiled(const float *x, const fl
 
 void launch_rmsnorm_tiled(const float *x, const float *gain, int H, float eps, int M, uint16_t *xh,
                           uint16_t *xl, hipStream_t s) {
-    // M is a multiple of 16 (chunk rows are padded to 32 per sequence)
     hipLaunchKernelGGL(k_rmsnorm_tiled, dim3((M + 15) / 16), dim3(1024), 0, s, x, gain, H, eps, M, xh, xl);
 }
 

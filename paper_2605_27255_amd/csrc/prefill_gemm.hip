@@ -23,11 +23,21 @@ template <int EPI>
 __device__ __forceinline__ void gemm_epi(const GemmParams &p, f32x4 a, f32x4 c, int strip, int m) {
     const int h = (threadIdx.x >> 5) & 1;
     if (strip >= (p.N >> 4) || m >= p.M) return;
-    const int b = m / p.g.mpad, i = m - b * p.g.mpad;
-    // Rows past the chunk or past a ragged batch's shorter prompt hold nothing:
-    // their X may be stale (a tile of another shape was skipped there), and the
-    // cache keeps finite values at positions no prompt has reached.
-    if (i >= p.g.clen || (p.g.ntok && p.g.c0 + i >= seq_positions(p.g, b))) return;
+    int b, i, pos;
+    if (p.dpos) {   // a decode step: one row per sequence
+        if (m >= p.rows) return;
+        b = m;
+        i = 0;
+        pos = EPI == EPI_QKV ? p.dpos[m] : 0;
+    } else {
+        b = m / p.g.mpad;
+        i = m - b * p.g.mpad;
+        pos = p.g.c0 + i;
+        // Rows past the chunk or past a ragged batch's shorter prompt hold nothing:
+        // their X may be stale (a tile of another shape was skipped there), and the
+        // cache keeps finite values at positions no prompt has reached.
+        if (i >= p.g.clen || (p.g.ntok && pos >= seq_positions(p.g, b))) return;
+    }
     const int row0 = strip * 16 + 4 * h;
     if (EPI == EPI_STORE) {
         if (p.bias) {
@@ -39,8 +49,28 @@ __device__ __forceinline__ void gemm_epi(const GemmParams &p, f32x4 a, f32x4 c, 
         *(f32x4 *)(o + 8) = c;
     } else if (EPI == EPI_RESID) {
         float *o = p.out + (int64_t)m * p.N + row0;
-        *(f32x4 *)o = *(const f32x4 *)o + a;
-        *(f32x4 *)(o + 8) = *(const f32x4 *)(o + 8) + c;
+        a += *(const f32x4 *)o;
+        c += *(const f32x4 *)(o + 8);
+        *(f32x4 *)o = a;
+        *(f32x4 *)(o + 8) = c;
+        if (p.ss_out) {
+            float sq = (a[0] * a[0] + a[1] * a[1]) + (a[2] * a[2] + a[3] * a[3]) + (c[0] * c[0] + c[1] * c[1]) +
+                       (c[2] * c[2] + c[3] * c[3]);
+            sq += __shfl_xor(sq, 32);   // the strip's other eight rows (the same token: both lanes are here)
+            if (h == 0) p.ss_out[(int64_t)m * (p.N >> 4) + strip] = sq;
+        }
+        if (p.xn_hi) {
+            const f32x4 ga = *(const f32x4 *)(p.gain + row0), gc = *(const f32x4 *)(p.gain + row0 + 8);
+            const float f[8] = {a[0] * ga[0], a[1] * ga[1], a[2] * ga[2], a[3] * ga[3],
+                                c[0] * gc[0], c[1] * gc[1], c[2] * gc[2], c[3] * gc[3]};
+            u32x4 hi, lo;
+            split8(f, hi, lo);
+            const int64_t at = tiled_index(m, row0, p.N);          // row0 + 8: the next 16 lanes' pieces
+            *(u32x2 *)(p.xn_hi + at) = u32x2{hi[0], hi[1]};
+            *(u32x2 *)(p.xn_lo + at) = u32x2{lo[0], lo[1]};
+            *(u32x2 *)(p.xn_hi + at + 128) = u32x2{hi[2], hi[3]};
+            *(u32x2 *)(p.xn_lo + at + 128) = u32x2{lo[2], lo[3]};
+        }
     } else if (EPI == EPI_SILU) {
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
@@ -62,7 +92,6 @@ __device__ __forceinline__ void gemm_epi(const GemmParams &p, f32x4 a, f32x4 c, 
     } else if (EPI == EPI_QKV) {
         const int d = p.d, hs = d >> 4;
         const int qs = p.n_q * hs, ks = p.n_kv * hs;
-        const int pos = p.g.c0 + i;
         const int gs = strip + p.strip0;            // strip of the whole QKV matrix
         if (gs < qs + ks) {
             const bool isq = gs < qs;
@@ -80,7 +109,9 @@ __device__ __forceinline__ void gemm_epi(const GemmParams &p, f32x4 a, f32x4 c, 
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
                 const int dim0 = q ? (d >> 1) + jr : jr;
-                if (isq) {   // the query as a bf16 pair hi + lo (two planes)
+                if (isq && p.qf) {
+                    *(f32x4 *)(p.qf + ((int64_t)m * p.n_q + head) * d + dim0) = f32x4{r[q][0], r[q][1], r[q][2], r[q][3]};
+                } else if (isq) {   // the query as a bf16 pair hi + lo (two planes)
                     uint32_t hi[4], lo[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) split_bf(r[q][e], hi[e], lo[e]);
@@ -105,6 +136,29 @@ __device__ __forceinline__ void gemm_epi(const GemmParams &p, f32x4 a, f32x4 c, 
             }
         }
     }
+}
+
+// A decode step's RMSNorm scale of row m from its sum-of-squares parts: lane
+// (m, half h) adds its half of them in order, then the halves.
+template <int EPI>
+__device__ __forceinline__ float norm_scale(const GemmParams &p, int m) {
+    if (!(EPI == EPI_QKV || EPI == EPI_SWIGLU) || !p.ss_in) return 1.f;
+    const int h = (threadIdx.x >> 5) & 1, half = p.nss >> 1;
+    const float *q = p.ss_in + (int64_t)min(m, p.rows - 1) * p.nss + h * half;
+    float s = 0.f;
+    if ((p.nss & 7) == 0) {      // 16-byte pieces
+#pragma unroll 10
+        for (int i = 0; i < half; i += 4) {
+            const f32x4 v = *(const f32x4 *)(q + i);
+            s += (v[0] + v[1]) + (v[2] + v[3]);
+        }
+    } else {
+#pragma unroll 8
+        for (int i = 0; i < half; ++i) s += q[i];
+        if ((p.nss & 1) && h) s += q[half];
+    }
+    s += __shfl_xor(s, 32);
+    return rsqrtf(s / (float)p.K + p.eps);
 }
 
 // WR (weight rows) x WT (tokens) = four waves, each of NR x NT 32x32
@@ -270,6 +324,10 @@ __global__ __launch_bounds__(256, TL::MINW) void k_gemm(GemmParams p) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no load to LDS outlives the workgroup
 
     const int rb0 = wr * NR, tb0 = wt * NT;
+    float sc[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+        sc[j] = part ? 1.f : norm_scale<EPI>(p, bm * TL::TOKS + (tb0 + j) * 32 + (lane & 31));
 #pragma unroll
     for (int i = 0; i < NR; ++i)
 #pragma unroll
@@ -285,9 +343,10 @@ __global__ __launch_bounds__(256, TL::MINW) void k_gemm(GemmParams p) {
 #pragma unroll
                 for (int t = 0; t < 2; ++t)
                     gemm_epi<EPI>(p,
-                                  f32x4{acc[i][j][8 * t], acc[i][j][8 * t + 1], acc[i][j][8 * t + 2], acc[i][j][8 * t + 3]},
+                                  f32x4{acc[i][j][8 * t], acc[i][j][8 * t + 1], acc[i][j][8 * t + 2], acc[i][j][8 * t + 3]} *
+                                      sc[j],
                                   f32x4{acc[i][j][8 * t + 4], acc[i][j][8 * t + 5], acc[i][j][8 * t + 6],
-                                        acc[i][j][8 * t + 7]},
+                                        acc[i][j][8 * t + 7]} * sc[j],
                                   bn * RS + 2 * (rb0 + i) + t, bm * TL::TOKS + (tb0 + j) * 32 + (lane & 31));
             }
         }
@@ -324,7 +383,8 @@ __global__ __launch_bounds__(128) void k_gemm_fin(GemmParams p) {
                 c += v[k][1];
             }
     }
-    gemm_epi<EPI>(p, a, c, strip, m0 + (lane & 31));
+    const float sc = norm_scale<EPI>(p, m0 + (lane & 31));
+    gemm_epi<EPI>(p, a * sc, c * sc, strip, m0 + (lane & 31));
 }
 
 // `full` tiles whole, the others in ksplit ranges
@@ -341,7 +401,7 @@ static void launch_tile(const GemmParams &p, hipStream_t s) {
 // ---- tile shape and split --------------------------------------------------
 using TileL = GemmTile<4, 2, 2, 2, 2, 2>;   // 256 x 128, 64 KB of LDS, two workgroups per CU
 using TileM = GemmTile<2, 2, 2, 2, 2, 3>;   // 128 x 128, 48 KB, three
-using TileS = GemmTile<2, 1, 2, 2, 3, 4>;   // 128 x 64, 48 KB (three stages)
+using TileS = GemmTile<2, 1, 2, 2, 4, 2>;   // 128 x 64, 64 KB (four stages)
 using TileT = GemmTile<1, 1, 4, 1, 4, 4>;   // 128 x 32, 48 KB (four stages)
 
 // The shape and split with the shortest estimated time.  A CU runs the tiles
@@ -364,8 +424,8 @@ struct GemmPlan {
 };
 static GemmPlan gemm_plan(const GemmParams &p) {
     struct Shape { int rows, toks; double us; };
-    static const Shape shapes[4] = {{256, 128, 0.78}, {128, 128, 0.43}, {128, 64, 0.21}, {128, 32, 0.15}};
-    constexpr int kCU = 256, kMinTiles = 8;       // k tiles a range keeps at least
+    static const Shape shapes[4] = {{256, 128, 0.78}, {128, 128, 0.43}, {128, 64, 0.21}, {128, 32, 0.19}};
+    constexpr int kCU = 256, kMinTiles = 16;      // k tiles a range keeps at least
     constexpr double kFinUs = 4.0, kPartBytesPerUs = 5.5e6;
     const int KT = p.K >> 5;
     GemmPlan best{1, 0, 1};

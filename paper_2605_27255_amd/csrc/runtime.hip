@@ -499,11 +499,74 @@ static GemvParams gemv_base(const pipo_ctx *c, int B) {
     return p;
 }
 
+static AttnDecodeParams attn_params(const pipo_ctx *c, uint16_t *kc, uint16_t *vc) {
+    AttnDecodeParams ap{};
+    ap.q = c->qbuf; ap.kc = kc; ap.vc = vc; ap.kv_bstride = c->kv_bstride; ap.pos = c->pos;
+    ap.B = c->batch; ap.n_q = c->nq; ap.n_kv = c->nkv; ap.d = c->d; ap.lmax_pad = c->lmax_pad;
+    ap.splits = attn_splits(c, c->batch); ap.part = c->apart; ap.out = c->attn_out;
+    ap.xl_ctr = c->xl_merge && ap.splits != kAttnWgSplits && ap.splits <= kAttnXcdMergeMaxSplits ? c->xl_ctr : nullptr;
+    return ap;
+}
+
+// Sequences from which a decoder layer's matrices go through the tiled GEMM
+// (prefill_gemm.hip) instead of the decode GEMVs: past 16 the GEMVs stage two
+// or more column tiles of X per workgroup and cut K into ranges to do so,
+// while the tiled GEMM takes X from planes that the producing kernels write.
+// Four layers of the 4B (9B) width over 256 latents, one pair step in us,
+// GEMVs -> tiled GEMM: 24 sequences 480 -> 494 (652 -> 683), 32: 503 -> 515
+// (681 -> 699), 40: 598 -> 590 (795 -> 821), 48: 616 -> 603 (847 -> 837),
+// 64: 739 -> 648 (982 -> 900).
+constexpr int kTiledMinBatch = 41;
+
+// One decoder layer at the current positions, its matrices through the tiled
+// GEMM over the sequences' rows (padded to 32).  The residual epilogues write
+// the next GEMM's X (the new residual times the next RMSNorm's gain, without
+// its scale, which that GEMM's epilogue applies); `prepared`: the layer before
+// wrote this one's, with g_next its gain.
+static void enqueue_layer_tiled(pipo_ctx *c, const LayerW &lw, uint16_t *kc, uint16_t *vc, float *xres, float *ssres,
+                                bool prepared, const float *g_next, hipStream_t s) {
+    const int B = c->batch, H = c->H;
+    GemmParams gp{};
+    gp.M = (int)round_up(B, 32); gp.rows = B; gp.dpos = c->pos; gp.g.B = B;
+    gp.n_q = c->nq; gp.n_kv = c->nkv; gp.d = c->d; gp.lmax_pad = c->lmax_pad; gp.kv_bstride = c->kv_bstride;
+    gp.rope_cos = c->rope_cos; gp.rope_sin = c->rope_sin; gp.part = c->p_part; gp.part_cap = c->p_part_cap;
+    gp.nss = H / 16; gp.eps = c->cfg.rms_eps;
+    if (!prepared) {
+        PROF(PIPO_K_GEMV_LAYER);
+        launch_rmsnorm_tiled(xres, lw.g_attn, H, c->cfg.rms_eps, B, c->p_xn, c->p_xn_lo, s);
+    }
+    GemmParams p = gp;
+    p.W = lw.wqkv; p.X = c->p_xn; p.Xlo = c->p_xn_lo; p.N = c->nqkv; p.K = H; p.epi = EPI_QKV; p.qf = c->qbuf;
+    p.kc = kc; p.vc = vc; p.ss_in = prepared ? ssres : nullptr;
+    { PROF(PIPO_K_GEMV_LAYER); launch_gemm(p, s); }
+    AttnDecodeParams ap = attn_params(c, kc, vc);
+    ap.out_hi = c->p_o; ap.out_lo = c->p_o_lo;
+    { PROF(PIPO_K_ATTN_DECODE); launch_attn_decode(ap, s); }
+    p = gp;
+    p.W = lw.wo; p.X = c->p_o; p.Xlo = c->p_o_lo; p.N = H; p.K = c->qdim; p.epi = EPI_RESID; p.out = xres;
+    p.ss_out = ssres; p.gain = lw.g_ffn; p.xn_hi = c->p_xn; p.xn_lo = c->p_xn_lo;
+    { PROF(PIPO_K_GEMV_LAYER); launch_gemm(p, s); }
+    p = gp;
+    p.W = lw.wgu; p.X = c->p_xn; p.Xlo = c->p_xn_lo; p.N = 2 * c->F; p.K = H; p.epi = EPI_SWIGLU; p.ss_in = ssres;
+    p.act_hi = c->p_act; p.act_lo = c->p_act_lo;
+    { PROF(PIPO_K_GEMV_LAYER); launch_gemm(p, s); }
+    p = gp;
+    p.W = lw.wdown; p.X = c->p_act; p.Xlo = c->p_act_lo; p.N = H; p.K = c->F; p.epi = EPI_RESID; p.out = xres;
+    p.ss_out = ssres; p.gain = g_next; p.xn_hi = g_next ? c->p_xn : nullptr; p.xn_lo = c->p_xn_lo;
+    { PROF(PIPO_K_GEMV_LAYER); launch_gemm(p, s); }
+}
+
 // One decoder layer (eq. 2) at the current positions over the residual xres
 // (with its sum-of-squares parts ssres): a backbone layer, or the MTP head's.
+// `prev`: the layer run just before over the same residual; `next`: the one run
+// just after (NULL: none).
 static void enqueue_layer(pipo_ctx *c, const LayerW &lw, uint16_t *kc, uint16_t *vc, float *xres, float *ssres,
-                          hipStream_t s) {
+                          hipStream_t s, const LayerW *prev = nullptr, const LayerW *next = nullptr) {
     const int B = c->batch, H = c->H;
+    if (B >= kTiledMinBatch) {
+        enqueue_layer_tiled(c, lw, kc, vc, xres, ssres, prev != nullptr, next ? next->g_attn : nullptr, s);
+        return;
+    }
     const GemvParams base = gemv_base(c, B);
     GemvParams p = base;
     p.W = lw.wqkv; p.N = c->nqkv; p.K = H;
@@ -514,15 +577,11 @@ static void enqueue_layer(pipo_ctx *c, const LayerW &lw, uint16_t *kc, uint16_t 
     p.deferred = (c->nq / c->nkv) * c->d <= 1024 ? &ranges : nullptr;   // the attention stages q in 4 KB of LDS
     { PROF_GEMV(PIPO_K_GEMV_LAYER); gemv(c, p, PRO_NORM, EPI_QKV, s); }
 
-    AttnDecodeParams ap{};
-    ap.q = c->qbuf; ap.kc = kc; ap.vc = vc; ap.kv_bstride = c->kv_bstride; ap.pos = c->pos;
+    AttnDecodeParams ap = attn_params(c, kc, vc);
     if (ranges > 1) {
         ap.qkv_part = p.part; ap.ksplit = ranges; ap.nqkv = c->nqkv;
         ap.rope_cos = c->rope_cos; ap.rope_sin = c->rope_sin;
     }
-    ap.B = B; ap.n_q = c->nq; ap.n_kv = c->nkv; ap.d = c->d; ap.lmax_pad = c->lmax_pad;
-    ap.splits = attn_splits(c, B); ap.part = c->apart; ap.out = c->attn_out;
-    ap.xl_ctr = c->xl_merge && ap.splits != kAttnWgSplits && ap.splits <= kAttnXcdMergeMaxSplits ? c->xl_ctr : nullptr;
     { PROF(PIPO_K_ATTN_DECODE); launch_attn_decode(ap, s); }
 
     p = base;
@@ -543,7 +602,8 @@ static void enqueue_layer(pipo_ctx *c, const LayerW &lw, uint16_t *kc, uint16_t 
 static void enqueue_layers(pipo_ctx *c, hipStream_t s) {
     for (int l = 0; l < c->L; ++l)
         enqueue_layer(c, c->layers[l], c->kc + (int64_t)l * c->Bmax * c->kv_bstride,
-                      c->vc + (int64_t)l * c->Bmax * c->kv_bstride, c->x, c->ss_x, s);
+                      c->vc + (int64_t)l * c->Bmax * c->kv_bstride, c->x, c->ss_x, s, l > 0 ? &c->layers[l - 1] : nullptr,
+                      l + 1 < c->L ? &c->layers[l + 1] : nullptr);
 }
 
 // Selection of one slot's tokens from `logits` into `best`.  `in_pair`: the
