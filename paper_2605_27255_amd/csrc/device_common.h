@@ -57,6 +57,21 @@ __device__ __forceinline__ f32x4 mfma16(u32x4 a, u32x4 b, f32x4 c) {
                                                    __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
+// Two floats into one fp16x2 word, rounded to nearest even.
+typedef __attribute__((ext_vector_type(2))) _Float16 f16x2_t;
+__device__ __forceinline__ uint32_t pack_f16x2(float lo, float hi) {
+    const f16x2_t v = {(_Float16)lo, (_Float16)hi};
+    return __builtin_bit_cast(uint32_t, v);
+}
+// 16 bytes per lane from src + 16 lane (src uniform) to LDS byte address
+// lds + 16 lane.  Counted by vmcnt, which the compiler does not track here:
+// the caller waits for it explicitly.  (s_nop: one wait state between the
+// write of M0 and its use.)
+__device__ __forceinline__ void load_to_lds(const uint16_t *src, uint32_t lds, uint32_t lane16) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :: "s"(lds), "v"(lane16), "s"(src) : "memory");
+}
+
 // ---- wave reductions -------------------------------------------------------
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll

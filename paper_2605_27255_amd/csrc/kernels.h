@@ -222,8 +222,9 @@ struct GemmParams {
     int epi;                                // EPI_STORE (bias), EPI_RESID, EPI_SWIGLU, EPI_QKV, EPI_SILU
     PrefillGeom g;
     float *out; const float *bias; uint16_t *act_hi, *act_lo;
-    uint16_t *q, *q_lo;                     // EPI_QKV: the query as hi and lo planes
-    uint16_t *kc; uint16_t *vc;
+    uint16_t *q;                            // EPI_QKV: the query in fp16 [B][n_q][mpad][d]
+    uint16_t *kc; uint16_t *vc;             // ... keys and values into the cache and, if not NULL,
+    uint16_t *kh; uint16_t *vh;             // widened to fp16 (AttnPrefillParams)
     const float *rope_cos; const float *rope_sin;
     int n_q, n_kv, d, lmax_pad; int64_t kv_bstride;
     // A decode step's GEMM (dpos not NULL): row m is sequence m at position dpos[m],
@@ -241,8 +242,11 @@ struct GemmParams {
 };
 void launch_gemm(const GemmParams &p, hipStream_t s);
 struct AttnPrefillParams {
-    const uint16_t *q, *q_lo;   // bf16 [B][n_q][mpad][d] each: the query as hi + lo
+    const uint16_t *q;          // fp16 [B][n_q][mpad][d]
     const uint16_t *kc, *vc; int64_t kv_bstride;
+    // one layer's keys and values in fp16, addressed like the cache (V's 16-dim blocks in MFMA
+    // operand order); the chunk's own positions are in place, the earlier ones are widened here
+    uint16_t *kh, *vh;
     PrefillGeom g;
     int n_q, n_kv, d, lmax_pad;
     uint16_t *out_hi, *out_lo;  // tiled [B*mpad][n_q*d], hi and lo planes

@@ -111,16 +111,16 @@ __device__ __forceinline__ void gemm_epi(const GemmParams &p, f32x4 a, f32x4 c, 
                 const int dim0 = q ? (d >> 1) + jr : jr;
                 if (isq && p.qf) {
                     *(f32x4 *)(p.qf + ((int64_t)m * p.n_q + head) * d + dim0) = f32x4{r[q][0], r[q][1], r[q][2], r[q][3]};
-                } else if (isq) {   // the query as a bf16 pair hi + lo (two planes)
-                    uint32_t hi[4], lo[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) split_bf(r[q][e], hi[e], lo[e]);
+                } else if (isq) {   // the query in fp16, as the prefill attention takes it
                     const int64_t at = (((int64_t)b * p.n_q + head) * p.g.mpad + i) * d + dim0;
-                    *(u32x2 *)(p.q + at) = u32x2{hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16)};
-                    *(u32x2 *)(p.q_lo + at) = u32x2{lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16)};
-                } else {     // the key, stored in bf16 (the cache's format)
-                    *(u32x2 *)(p.kc + (int64_t)b * p.kv_bstride + (int64_t)head * p.lmax_pad * d +
-                               tiled_index(pos, dim0, d)) = u32x2{pack_bf2(r[q][0], r[q][1]), pack_bf2(r[q][2], r[q][3])};
+                    *(u32x2 *)(p.q + at) = u32x2{pack_f16x2(r[q][0], r[q][1]), pack_f16x2(r[q][2], r[q][3])};
+                } else {     // the key, stored in bf16 (the cache's format), and widened for the prefill attention
+                    const u32x2 w = u32x2{pack_bf2(r[q][0], r[q][1]), pack_bf2(r[q][2], r[q][3])};
+                    const int64_t at = (int64_t)b * p.kv_bstride + (int64_t)head * p.lmax_pad * d + tiled_index(pos, dim0, d);
+                    *(u32x2 *)(p.kc + at) = w;
+                    if (p.kh)
+                        *(u32x2 *)(p.kh + at) =
+                            u32x2{pack_f16x2(bf_lo(w[0]), bf_hi(w[0])), pack_f16x2(bf_lo(w[1]), bf_hi(w[1]))};
                 }
             }
         } else {
@@ -129,10 +129,17 @@ __device__ __forceinline__ void gemm_epi(const GemmParams &p, f32x4 a, f32x4 c, 
                 const f32x4 v = q ? c : a;
                 const int r0 = (gs - qs - ks) * 16 + 4 * h + 8 * q;
                 const int kvh = r0 / d, dim = r0 - kvh * d;
-                uint16_t *dst = p.vc + (int64_t)b * p.kv_bstride +
-                                ((int64_t)(kvh * (p.lmax_pad >> 5) + (pos >> 5)) * d + dim) * 32 + vslot(pos & 31);
+                const int64_t tile = (int64_t)b * p.kv_bstride + (int64_t)(kvh * (p.lmax_pad >> 5) + (pos >> 5)) * d * 32;
+                const int slot = vslot(pos & 31);
+                uint16_t *dst = p.vc + tile + dim * 32 + slot;
+                // widened: 16-dim blocks in operand order (slot group, dim, slot)
+                uint16_t *wide = p.vh ? p.vh + tile + (dim >> 4) * 512 + ((slot >> 3) * 16 + (dim & 15)) * 8 + (slot & 7) : nullptr;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) dst[e * 32] = (uint16_t)f2bf(v[e]);
+                for (int e = 0; e < 4; ++e) {
+                    const uint32_t w = f2bf(v[e]);
+                    dst[e * 32] = (uint16_t)w;
+                    if (wide) wide[e * 8] = __builtin_bit_cast(uint16_t, (_Float16)bf2f(w));
+                }
             }
         }
     }
@@ -208,15 +215,6 @@ __device__ __forceinline__ bool pad_rows(const GemmParams &p, int m0, int m1) {
         any = any || p.g.c0 + i0 < seq_positions(p.g, sb);
     }
     return !any;
-}
-
-// 16 bytes per lane from src + 16 lane (src uniform) to LDS byte address
-// lds + 16 lane.  Counted by vmcnt, which the compiler does not track here:
-// the loop below waits for it explicitly.  (s_nop: one wait state between the
-// write of M0 and its use.)
-__device__ __forceinline__ void load_to_lds(const uint16_t *src, uint32_t lds, uint32_t lane16) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "s"(lds), "v"(lane16), "s"(src) : "memory");
 }
 
 template <int EPI, bool HASLO, class TL>

@@ -80,7 +80,8 @@ struct pipo_ctx {
     SampState *samp_state;
     pipo_pair *out;
     // prefill activations
-    uint16_t *p_xin, *p_xn, *p_xn_lo, *p_q, *p_q_lo, *p_o, *p_o_lo, *p_act, *p_act_lo;
+    uint16_t *p_kh, *p_vh;     // one layer's keys and values in fp16 (prefill attention)
+    uint16_t *p_xin, *p_xn, *p_xn_lo, *p_q, *p_o, *p_o_lo, *p_act, *p_act_lo;
     float *p_x;
     float *p_part; int64_t p_part_cap;   // prefill GEMM k-range partial sums
 
@@ -365,7 +366,8 @@ extern "C" int pipo_init_weights(const pipo_config *cfg, uint64_t seed, void *st
         c->p_xn = a.take<uint16_t>(mcap * H);
         c->p_xn_lo = a.take<uint16_t>(mcap * H);
         c->p_q = a.take<uint16_t>(mcap * c->qdim);
-        c->p_q_lo = a.take<uint16_t>(mcap * c->qdim);
+        c->p_kh = a.take<uint16_t>((int64_t)B * c->kv_bstride);
+        c->p_vh = a.take<uint16_t>((int64_t)B * c->kv_bstride);
         c->p_o = a.take<uint16_t>(mcap * c->qdim);
         c->p_o_lo = a.take<uint16_t>(mcap * c->qdim);
         c->p_act = a.take<uint16_t>(mcap * F);
@@ -837,7 +839,8 @@ static int prefill_backbone(pipo_ctx *c, int32_t batch, const int32_t *d_tokens,
             p = gp;
             p.strip0 = kv_only ? c->qdim >> 4 : 0;
             p.W = lw.wqkv + (int64_t)p.strip0 * 16 * H; p.N = c->nqkv - p.strip0 * 16;
-            p.X = c->p_xn; p.Xlo = c->p_xn_lo; p.K = H; p.epi = EPI_QKV; p.q = c->p_q; p.q_lo = c->p_q_lo; p.kc = kc; p.vc = vc;
+            p.X = c->p_xn; p.Xlo = c->p_xn_lo; p.K = H; p.epi = EPI_QKV; p.q = c->p_q; p.kc = kc; p.vc = vc;
+            if (!kv_only) { p.kh = c->p_kh; p.vh = c->p_vh; }
             { PROF(PIPO_K_PREFILL_GEMM); launch_gemm(p, s); }
         };
         for (int l = 0; l < c->L; ++l) {
@@ -851,7 +854,7 @@ static int prefill_backbone(pipo_ctx *c, int32_t batch, const int32_t *d_tokens,
             }
             layer_qkv(lw, c->p_x, kc, vc, false);
             AttnPrefillParams ap{};
-            ap.q = c->p_q; ap.q_lo = c->p_q_lo; ap.kc = kc; ap.vc = vc; ap.kv_bstride = c->kv_bstride; ap.g = g;
+            ap.q = c->p_q; ap.kh = c->p_kh; ap.vh = c->p_vh; ap.kc = kc; ap.vc = vc; ap.kv_bstride = c->kv_bstride; ap.g = g;
             ap.n_q = c->nq; ap.n_kv = c->nkv; ap.d = c->d; ap.lmax_pad = c->lmax_pad; ap.out_hi = c->p_o; ap.out_lo = c->p_o_lo;
             { PROF(PIPO_K_PREFILL_ATTN); launch_attn_prefill(ap, s); }
             p = gp;
