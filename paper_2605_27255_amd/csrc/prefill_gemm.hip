@@ -422,9 +422,10 @@ struct GemmPlan {
 };
 static GemmPlan gemm_plan(const GemmParams &p) {
     struct Shape { int rows, toks; double us; };
-    static const Shape shapes[4] = {{256, 128, 0.78}, {128, 128, 0.43}, {128, 64, 0.21}, {128, 32, 0.19}};
+    static const Shape shapes[4] = {{256, 128, 0.78}, {128, 128, 0.43}, {128, 64, 0.25}, {128, 32, 0.21}};
     constexpr int kCU = 256, kMinTiles = 16;      // k tiles a range keeps at least
-    constexpr double kFinUs = 4.0, kPartBytesPerUs = 5.5e6;
+    constexpr double kPartBytesPerUs = 3.5e6;
+    const double fin_us = p.ss_in ? 9.0 : 5.0;    // (with the RMSNorm scale to form)
     const int KT = p.K >> 5;
     GemmPlan best{1, 0, 1};
     double tbest = 1e30;
@@ -439,7 +440,7 @@ static GemmPlan gemm_plan(const GemmParams &p) {
             const int64_t units = rest * R;
             double steps = (double)((full + kCU - 1) / kCU) * KT + (double)((units + kCU - 1) / kCU) * ((KT + R - 1) / R);
             if (full + units <= kCU) steps *= 1.25;
-            const double t = steps * us + (R > 1 ? kFinUs + 8.0 * units * c.rows * c.toks / kPartBytesPerUs : 0.0);
+            const double t = steps * us + (R > 1 ? fin_us + 8.0 * units * c.rows * c.toks / kPartBytesPerUs : 0.0);
             if (t < tbest) tbest = t, best = GemmPlan{sh, (int)full, R};
         }
     }
