@@ -422,9 +422,9 @@ struct GemmPlan {
 };
 static GemmPlan gemm_plan(const GemmParams &p) {
     struct Shape { int rows, toks; double us; };
-    static const Shape shapes[4] = {{256, 128, 0.78}, {128, 128, 0.43}, {128, 64, 0.25}, {128, 32, 0.21}};
+    static const Shape shapes[4] = {{256, 128, 0.78}, {128, 128, 0.48}, {128, 64, 0.25}, {128, 32, 0.21}};
     constexpr int kCU = 256, kMinTiles = 16;      // k tiles a range keeps at least
-    constexpr double kPartBytesPerUs = 3.5e6;
+    constexpr double kPartBytesPerUs = 6e6;
     const double fin_us = p.ss_in ? 9.0 : 5.0;    // (with the RMSNorm scale to form)
     const int KT = p.K >> 5;
     GemmPlan best{1, 0, 1};
@@ -438,7 +438,9 @@ static GemmPlan gemm_plan(const GemmParams &p) {
             const int64_t full = R == 1 ? tiles : tiles / kCU * kCU, rest = tiles - full;
             if (R > 1 && (!rest || rest * R * c.rows * c.toks > p.part_cap)) continue;
             const int64_t units = rest * R;
-            double steps = (double)((full + kCU - 1) / kCU) * KT + (double)((units + kCU - 1) / kCU) * ((KT + R - 1) / R);
+            double steps = (double)((full + kCU - 1) / kCU) * KT;
+            // (split units next to whole tiles do not spread over the CUs quite evenly)
+            if (R > 1) steps += (full ? 1.3 : 1.0) * ((units + kCU - 1) / kCU) * ((KT + R - 1) / R);
             if (full + units <= kCU) steps *= 1.25;
             const double t = steps * us + (R > 1 ? fin_us + 8.0 * units * c.rows * c.toks / kPartBytesPerUs : 0.0);
             if (t < tbest) tbest = t, best = GemmPlan{sh, (int)full, R};
