@@ -186,59 +186,89 @@ __device__ __forceinline__ uint32_t order_key(float f) {
 // (wave, sub-tile, lane, element).
 constexpr int kSampWaves = kSampThreads / 64;
 
-template <bool EVAL>
-__global__ __launch_bounds__(kSampThreads) void k_sample(SampleParams p) {
-    __shared__ unsigned long long hist[kSampWaves][256];
-    __shared__ float s_red[kSampWaves];
-    __shared__ unsigned long long s_u64[kSampWaves];
-    __shared__ uint32_t s_prefix;
-    __shared__ unsigned long long s_above, s_mass;
-    __shared__ int s_all;
+struct SampShared {
+    unsigned long long hist[kSampWaves][256];
+    float s_red[kSampWaves];
+    unsigned long long s_u64[kSampWaves];
+    unsigned long long s_suf[257], s_wtot[4];
+    unsigned long long s_above, s_mass;
+    uint32_t s_prefix, s_kpre, s_krem;
+    int s_all, s_dig;
+};
+
+// Ids penalised besides the bitmap: the step's input pair (the second unless
+// PAD) and the extra token; -1: none.
+struct PenalExtra { int id[3]; };
+__device__ __forceinline__ PenalExtra penal_extra(const SampleParams &p, int b) {
+    PenalExtra x{{-1, -1, -1}};
+    if (p.pairs) {
+        x.id[0] = p.pairs[2 * b];
+        x.id[1] = p.pairs[2 * b + 1] == p.pad_id ? -1 : p.pairs[2 * b + 1];
+    }
+    if (p.extra_key) x.id[2] = argmax_key_id(p.extra_key[b]);
+    return x;
+}
+// The penalty on the four logits of ids id .. id + 3, kept in the row `pen`.
+__device__ __forceinline__ void penalise4(const SampleParams &p, const uint32_t *seen, const PenalExtra &x, int id,
+                                          float (&v)[4], float *pen) {
+    const uint32_t bits = (seen && id < p.V) ? seen[id >> 5] >> (id & 31) : 0u;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int j = id + e;
+        if (((bits >> e) & 1u) || j == x.id[0] || j == x.id[1] || j == x.id[2])
+            v[e] = v[e] > 0.f ? v[e] / p.rep_penalty : v[e] * p.rep_penalty;
+    }
+    if (id + 3 < p.V) *(float4 *)(pen + id) = make_float4(v[0], v[1], v[2], v[3]);
+}
+
+// LIST: the row is a list of n penalised (value, id) candidates in id order
+// (every token the top-k keeps is among them) instead of the V logits.
+template <bool EVAL, bool LIST>
+__device__ __forceinline__ void sample_row(const SampleParams &p, SampShared &sh, const float *lval, const int *lid, int n) {
+    static_assert(EVAL || !LIST, "lists come from the evaluation sampler");
+    auto &hist = sh.hist;
+    auto &s_red = sh.s_red;
+    auto &s_u64 = sh.s_u64;
+    auto &s_suf = sh.s_suf;
+    auto &s_wtot = sh.s_wtot;
+    auto &s_dig = sh.s_dig;
+    auto &s_prefix = sh.s_prefix;
+    auto &s_above = sh.s_above;
+    auto &s_mass = sh.s_mass;
+    auto &s_all = sh.s_all;
 
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const float *lg = p.logits + (int64_t)b * p.V;
-    const int V = p.V;
+    const int V = LIST ? n : p.V;
     const int R = ((V + kSampWaves * 256 - 1) / (kSampWaves * 256)) * 256;   // ids per wave
     const int w0 = wave * R;
-    // penalised ids besides the bitmap: the step's input pair (the second
-    // unless PAD) and the extra token; -1: none
-    int ex0 = -1, ex1 = -1, ex2 = -1;
+    PenalExtra extra{{-1, -1, -1}};
     const uint32_t *seen = nullptr;
-    if constexpr (EVAL) {
+    if constexpr (EVAL && !LIST) {
         if (p.seen) seen = p.seen + (int64_t)b * p.seen_words;
-        if (p.pairs) {
-            ex0 = p.pairs[2 * b];
-            ex1 = p.pairs[2 * b + 1] == p.pad_id ? -1 : p.pairs[2 * b + 1];
-        }
-        if (p.extra_key) ex2 = argmax_key_id(p.extra_key[b]);
+        extra = penal_extra(p, b);
     }
     // The four logits of this lane in sub-tile t (ids past V read id 0,
     // masked).  EVAL: the first pass reads the raw logits, applies the
     // penalty and keeps the penalised row in p.pen (each lane rereads only
     // what it wrote itself); every later pass reads that row.
     const float *src = lg;
-    float *pen = EVAL ? p.pen + (int64_t)b * V : nullptr;
+    float *pen = EVAL && !LIST ? p.pen + (int64_t)b * V : nullptr;
     auto load4 = [&](int t, float (&v)[4]) {
         const int id = w0 + t * 256 + 4 * lane;
+        if constexpr (LIST) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = lval[id + e < V ? id + e : 0];
+            return;
+        }
         const float4 q = *(const float4 *)(src + (id + 3 < V ? id : 0));
         v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-    };
-    auto penalise = [&](int t, float (&v)[4]) {
-        const int id = w0 + t * 256 + 4 * lane;
-        const uint32_t bits = (seen && id < V) ? seen[id >> 5] >> (id & 31) : 0u;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int j = id + e;
-            if (((bits >> e) & 1u) || j == ex0 || j == ex1 || j == ex2)
-                v[e] = v[e] > 0.f ? v[e] / p.rep_penalty : v[e] * p.rep_penalty;
-        }
-        if (id + 3 < V) *(float4 *)(pen + id) = make_float4(v[0], v[1], v[2], v[3]);
     };
     // V is a multiple of 16, so a lane's four ids are all in range or all out.
     // Conditions are combined with & and masses masked arithmetically (no
     // short-circuit, no select around a load's use): otherwise the compiler
     // sinks each load into its branch and a pass keeps one load in flight.
-    auto valid = [&](int t, int e) { (void)e; return w0 + t * 256 + 4 * lane < V; };
+    auto valid = [&](int t, int e) { return w0 + t * 256 + 4 * lane + (LIST ? e : 0) < V; };
     auto masked = [](bool ok, uint64_t m) { return m & (0ull - (uint64_t)ok); };
     const int nt = R / 256;
     // every pass: four sub-tiles' loads issued together, then their use
@@ -261,8 +291,6 @@ __global__ __launch_bounds__(kSampThreads) void k_sample(SampleParams p) {
     // into s_suf (threads 0..255, a reversed wave scan); then each bin tests
     // its own suffix, so the digit is one parallel step instead of a serial
     // 256-step scan.
-    __shared__ unsigned long long s_suf[257], s_wtot[4];
-    __shared__ int s_dig;
     auto suffix_sums = [&]() {
         unsigned long long x = 0;
         if (tid < 256) {
@@ -285,11 +313,11 @@ __global__ __launch_bounds__(kSampThreads) void k_sample(SampleParams p) {
     float mx = -INFINITY;
     for_tiles([&](int t, const float (&v0)[4]) {
         float v[4] = {v0[0], v0[1], v0[2], v0[3]};
-        if constexpr (EVAL) penalise(t, v);
+        if constexpr (EVAL && !LIST) penalise4(p, seen, extra, w0 + t * 256 + 4 * lane, v, pen);
 #pragma unroll
         for (int e = 0; e < 4; ++e) mx = fmaxf(mx, valid(t, e) ? v[e] : -INFINITY);
     });
-    if constexpr (EVAL) src = pen;
+    if constexpr (EVAL && !LIST) src = pen;
     mx = wave_max(mx);
     if (lane == 0) s_red[wave] = mx;
     __syncthreads();
@@ -301,7 +329,8 @@ __global__ __launch_bounds__(kSampThreads) void k_sample(SampleParams p) {
     uint32_t kstar = 0;
     if constexpr (EVAL) {
         if (p.top_k > 0 && p.top_k < V) {
-            __shared__ uint32_t s_kpre, s_krem;
+            auto &s_kpre = sh.s_kpre;
+            auto &s_krem = sh.s_krem;
             if (tid == 0) { s_kpre = 0; s_krem = (uint32_t)p.top_k; }
             for (int pass = 0; pass < 4; ++pass) {
                 const int shift = 24 - 8 * pass;
@@ -447,7 +476,8 @@ __global__ __launch_bounds__(kSampThreads) void k_sample(SampleParams p) {
             for (int e = 0; e < 4; ++e) {
                 r += m4[e];
                 if (m4[e] > 0 && r > tsel) {
-                    p.best[b] = (1ull << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)(w0 + t * 256 + 4 * lane + e));
+                    const int at = w0 + t * 256 + 4 * lane + e;
+                    p.best[b] = (1ull << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)(LIST ? lid[at] : at));
                     break;
                 }
             }
@@ -455,6 +485,177 @@ __global__ __launch_bounds__(kSampThreads) void k_sample(SampleParams p) {
         run += __shfl(inc, 63);
         if (run > tsel) break;
     }
+}
+
+template <bool EVAL>
+__global__ __launch_bounds__(kSampThreads) void k_sample(SampleParams p) {
+    __shared__ SampShared sh;
+    sample_row<EVAL, false>(p, sh, nullptr, nullptr, 0);
+}
+
+// ---------------------------------------------------------------------------
+// Evaluation sampler with top-k, the row split over nseg workgroups.  The
+// whole-row kernel reads the row a dozen times with one workgroup, which at a
+// few sequences leaves most of the chip idle (4B, 8 sequences: 258 us a call).
+// k_sample_cand: each workgroup penalises its segment of ids, finds the
+// segment's own k-th largest value (the same radix select) and lists the
+// tokens at or above it (ties included) in id order; the row's k largest, with
+// their ties, are all among the segments' lists.  k_sample_list runs the
+// whole-row selection over the listed candidates (about nseg k of them, in
+// LDS), with the same arithmetic, so the same token.  Should the ties of a
+// segment not fit its list, the row is selected from the logits as before.
+constexpr int kListMax = kSampCandidates;    // candidates of a row
+
+template <int NTH>
+__global__ __launch_bounds__(NTH) void k_sample_cand(SampleParams p) {
+    constexpr int NWV = NTH / 64;
+    __shared__ uint32_t hist[NWV][256];
+    __shared__ uint32_t s_suf[257], s_wtot[4], s_cnt[NWV];
+    __shared__ int s_dig;
+    const int nseg = p.nseg, V = p.V, cap = kListMax / nseg;
+    const int b = blockIdx.x / nseg, seg = blockIdx.x - b * nseg;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int RW = p.seg_len / NWV, nt = RW / 256;            // ids per wave (a multiple of 256), its sub-tiles
+    const int w0 = seg * p.seg_len + wave * RW;
+    const float *src = p.logits + (int64_t)b * V;
+    float *pen = p.pen + (int64_t)b * V;
+    const uint32_t *seen = p.seen ? p.seen + (int64_t)b * p.seen_words : nullptr;
+    const PenalExtra extra = penal_extra(p, b);
+    auto for_tiles = [&](auto &&f) {
+        int t = 0;
+        for (; t + 4 <= nt; t += 4) {
+            float4 q[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int id = w0 + (t + u) * 256 + 4 * lane;
+                q[u] = *(const float4 *)(src + (id < V ? id : 0));
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                float v[4] = {q[u].x, q[u].y, q[u].z, q[u].w};
+                f(w0 + (t + u) * 256 + 4 * lane, v);
+            }
+        }
+        for (; t < nt; ++t) {
+            const int id = w0 + t * 256 + 4 * lane;
+            const float4 q = *(const float4 *)(src + (id < V ? id : 0));
+            float v[4] = {q.x, q.y, q.z, q.w};
+            f(id, v);
+        }
+    };
+    uint32_t prefix = 0, krem = (uint32_t)p.top_k;
+    for (int pass = 0; pass < 4; ++pass) {
+        const int shift = 24 - 8 * pass;
+        for (int i = tid; i < NWV * 256; i += NTH) (&hist[0][0])[i] = 0;
+        if (tid == 0) { s_dig = -1; s_suf[256] = 0; }
+        __syncthreads();
+        for_tiles([&](int id, float (&v)[4]) {
+            if (pass == 0) penalise4(p, seen, extra, id, v, pen);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t key = order_key(v[e]);
+                if ((id < V) & ((pass == 0) | ((key >> ((shift + 8) & 31)) == prefix)))
+                    atomicAdd(&hist[wave][(key >> shift) & 255u], 1u);
+            }
+        });
+        src = pen;           // (each lane rereads only what it wrote itself)
+        __syncthreads();
+        uint32_t x = 0;
+        if (tid < 256) {     // suffix sums of the merged histogram
+            for (int w = 0; w < NWV; ++w) x += hist[w][255 - tid];
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint32_t y = __shfl_up(x, d);
+                if (lane >= d) x += y;
+            }
+            if (lane == 63) s_wtot[wave] = x;
+        }
+        __syncthreads();
+        if (tid < 256) {
+            for (int w = 0; w < wave; ++w) x += s_wtot[w];
+            s_suf[255 - tid] = x;
+            // the digit holding the rank-krem element: the largest d with S_d >= krem
+            if (x >= krem) atomicMax(&s_dig, 255 - tid);
+        }
+        __syncthreads();
+        const int d = s_dig < 0 ? 0 : s_dig;     // (fewer than krem left: all of them)
+        krem -= min(krem, s_suf[d + 1]);
+        prefix = s_dig < 0 ? 0u : (prefix << 8) | (uint32_t)d;
+        const bool all = s_dig < 0;
+        __syncthreads();
+        if (all) break;
+    }
+    const uint32_t kstar = prefix;
+    uint32_t cnt = 0;
+    for_tiles([&](int id, float (&v)[4]) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) cnt += (id < V) & (order_key(v[e]) >= kstar);
+    });
+    for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o);
+    if (lane == 0) s_cnt[wave] = cnt;
+    __syncthreads();
+    int at = 0, total = 0;
+    for (int w = 0; w < NWV; ++w) {
+        at += w < wave ? (int)s_cnt[w] : 0;
+        total += (int)s_cnt[w];
+    }
+    const int64_t base = ((int64_t)b * nseg + seg) * cap;
+    if (tid == 0) p.cand_n[b * nseg + seg] = total;
+    if (cnt == 0) return;    // (uniform in a wave; no barrier follows)
+    for_tiles([&](int id, float (&v)[4]) {
+        uint32_t m = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) m |= (uint32_t)((id < V) & (order_key(v[e]) >= kstar)) << e;
+        if (!__any(m != 0)) return;
+        int inc = __popc(m);
+        for (int d = 1; d < 64; d <<= 1) {
+            const int y = __shfl_up(inc, d);
+            if (lane >= d) inc += y;
+        }
+        int q = at + inc - __popc(m);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if ((m >> e) & 1u) {
+                if (q < cap) {
+                    p.cand_val[base + q] = v[e];
+                    p.cand_id[base + q] = id + e;
+                }
+                ++q;
+            }
+        at += __shfl(inc, 63);
+    });
+}
+
+__global__ __launch_bounds__(kSampThreads) void k_sample_list(SampleParams p) {
+    __shared__ SampShared sh;
+    __shared__ float s_val[kListMax];
+    __shared__ int s_id[kListMax];
+    __shared__ int s_off[kSampSegments + 1];
+    const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int nseg = p.nseg, cap = kListMax / nseg;
+    if (threadIdx.x == 0) {
+        int o = 0;
+        for (int sg = 0; sg < nseg; ++sg) {
+            const int c = p.cand_n[b * nseg + sg];
+            s_off[sg] = o;
+            o = (c > cap || o < 0) ? -1 : o + c;
+        }
+        s_off[nseg] = o;
+    }
+    __syncthreads();
+    const int n = s_off[nseg];
+    if (n < 0) {     // a segment's ties did not fit its list
+        sample_row<true, false>(p, sh, nullptr, nullptr, 0);
+        return;
+    }
+    for (int sg = wave; sg < nseg; sg += kSampWaves) {
+        const int64_t base = ((int64_t)b * nseg + sg) * cap;
+        for (int i = lane; i < s_off[sg + 1] - s_off[sg]; i += 64) {
+            s_val[s_off[sg] + i] = p.cand_val[base + i];
+            s_id[s_off[sg] + i] = p.cand_id[base + i];
+        }
+    }
+    __syncthreads();
+    sample_row<true, true>(p, sh, s_val, s_id, n);
 }
 
 // ---------------------------------------------------------------------------
@@ -661,11 +862,19 @@ __global__ __launch_bounds__(kSegThreads) void k_sample_seg(SampleParams p) {
 // Rows split over the segmented kernels: about 256 workgroups in all, 4 to 32 per row.
 int sample_segments(int B) {
     int n = 256 / (B > 0 ? B : 1);
-    return n < 4 ? 4 : (n > 32 ? 32 : n);
+    return n < 4 ? 4 : (n > kSampSegments ? kSampSegments : n);
 }
 
 void launch_sample(const SampleParams &p, hipStream_t s) {
-    if (p.top_k > 0 || p.rep_penalty != 1.f) {
+    if (p.cand_val && p.top_k > 0 && p.top_k < p.V && p.top_k <= kListMax / p.nseg) {
+        // segments of whole sub-tiles per wave; sixteen waves where a segment is long
+        SampleParams q = p;
+        const int per = (p.V + p.nseg - 1) / p.nseg, unit = per > 8192 ? 4096 : 1024;
+        q.seg_len = (per + unit - 1) / unit * unit;
+        if (unit == 4096) hipLaunchKernelGGL(k_sample_cand<1024>, dim3(p.B * p.nseg), dim3(1024), 0, s, q);
+        else hipLaunchKernelGGL(k_sample_cand<256>, dim3(p.B * p.nseg), dim3(256), 0, s, q);
+        hipLaunchKernelGGL(k_sample_list, dim3(p.B), dim3(kSampThreads), 0, s, q);
+    } else if (p.top_k > 0 || p.rep_penalty != 1.f) {
         hipLaunchKernelGGL(k_sample<true>, dim3(p.B), dim3(kSampThreads), 0, s, p);
     } else if (p.hist && p.nseg > 0) {
         SampleParams q = p;

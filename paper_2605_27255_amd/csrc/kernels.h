@@ -146,6 +146,8 @@ struct SampState {
     int all;                     // no value reached top_p (rounding): every token is in the nucleus
     unsigned long long above, mass, total;   // fixed-point masses above the prefix, of the nucleus, of the row
 };
+constexpr int kSampSegments = 32;        // workgroups a row is split over at most
+constexpr int kSampCandidates = 2048;    // top-k candidates of a row (all segments)
 struct SampleParams {
     const float *logits; int V; int B;
     float temperature, top_p;
@@ -157,6 +159,8 @@ struct SampleParams {
     const int32_t *pairs; int32_t pad_id;   // the step's input pair, also penalised (NULL: none)
     const uint64_t *extra_key;              // argmax key of one more penalised token (NULL: none)
     float *pen;                             // workspace [B][V]: the penalised logits
+    // top-k candidates of each segment [B][kSampCandidates] (NULL: one workgroup per row)
+    float *cand_val; int *cand_id; int *cand_n;   // cand_n [B][nseg]
     // temperature + top-p split over nseg workgroups per row (NULL hist: one
     // workgroup per row); best[b] must hold the row's argmax key on entry
     int nseg, seg_len;                      // seg_len is set by launch_sample

@@ -75,6 +75,7 @@ struct pipo_ctx {
     uint64_t *best_b, *best_d, *seeds;
     int32_t *pairs, *pos, *step;
     uint32_t *seen; int seen_words;   // penalised-token bitmap per sequence (evaluation sampler)
+    float *cand_val; int *cand_id, *cand_n;   // top-k candidates (evaluation sampler workspace)
     float *pen;                       // penalised logits [Bmax][V] (evaluation sampler workspace)
     unsigned long long *samp_hist, *samp_wmass;   // segmented top-p workspace: histograms, wave masses
     SampState *samp_state;
@@ -351,6 +352,9 @@ extern "C" int pipo_init_weights(const pipo_config *cfg, uint64_t seed, void *st
         c->seen_words = (V + 31) / 32;
         c->seen = a.take<uint32_t>((int64_t)B * c->seen_words);
         c->pen = a.take<float>((int64_t)B * V);
+        c->cand_val = a.take<float>((int64_t)B * kSampCandidates);
+        c->cand_id = a.take<int>((int64_t)B * kSampCandidates);
+        c->cand_n = a.take<int>((int64_t)B * kSampSegments);
         // at most 256 workgroups over the rows: sample_segments(B) * B <= 256
         c->samp_hist = a.take<unsigned long long>((int64_t)256 * 4 * 256);
         c->samp_wmass = a.take<unsigned long long>((int64_t)256 * 4);
@@ -622,7 +626,7 @@ static SampleParams sample_params(pipo_ctx *c, const float *logits, int B, int s
         sp.seen = c->seen; sp.seen_words = c->seen_words;
         sp.pairs = in_pair ? c->pairs : nullptr; sp.pad_id = c->pad_id;
         sp.extra_key = extra;
-        sp.pen = c->pen;
+        sp.pen = c->pen; sp.cand_val = c->cand_val; sp.cand_id = c->cand_id; sp.cand_n = c->cand_n;
     }
     return sp;
 }
