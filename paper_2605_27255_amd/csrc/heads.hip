@@ -25,6 +25,27 @@ void launch_seen_mark(const int32_t *tokens, int n, const int32_t *ntok, int B, 
     hipLaunchKernelGGL(k_seen_mark, dim3((n + 255) / 256, B), dim3(256), 0, s, tokens, n, ntok, V, seen, seen_words);
 }
 
+// A step's results to the caller's buffers in one launch: n0 words and two
+// arrays of 16-byte pieces.
+__global__ __launch_bounds__(256) void k_copy_out(uint32_t *d0, const uint32_t *s0, int n0, u32x4 *d1, const u32x4 *s1,
+                                                  int64_t n1, u32x4 *d2, const u32x4 *s2, int64_t n2) {
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < n0; i += 256) d0[i] = s0[i];
+    for (int64_t i = blockIdx.x * 256ll + threadIdx.x; i < n1 + n2; i += gridDim.x * 256ll) {
+        if (i < n1) d1[i] = s1[i];
+        else d2[i - n1] = s2[i - n1];
+    }
+}
+
+void launch_copy_out(void *d0, const void *s0, int n0, float *d1, const float *s1, int64_t n1, float *d2,
+                     const float *s2, int64_t n2, hipStream_t s) {
+    const int64_t v = (n1 + n2) >> 2;
+    int64_t grid = (v + 255) / 256;
+    grid = grid < 1 ? 1 : (grid > 4096 ? 4096 : grid);
+    hipLaunchKernelGGL(k_copy_out, dim3((unsigned)grid), dim3(256), 0, s, (uint32_t *)d0, (const uint32_t *)s0, n0,
+                       (u32x4 *)d1, (const u32x4 *)s1, n1 >> 2, (u32x4 *)d2, (const u32x4 *)s2, n2 >> 2);
+}
+
 struct PairOut { int32_t tok_b, tok_d; float conf; int32_t accept; };
 
 // One workgroup per sequence: s = w_c . RMSNorm([h_b; h_d]) * g_c,
@@ -711,6 +732,7 @@ __global__ __launch_bounds__(kSegThreads) void k_sample_seg(SampleParams p) {
             unsigned long long x = 0;
             if (tid < 256) {
                 unsigned long long h = 0;
+#pragma unroll 8
                 for (int sg = 0; sg < nseg; ++sg) h += H[((PASS - 1) * nseg + sg) * 256 + (255 - tid)];
                 x = h;
                 for (int d = 1; d < 64; d <<= 1) {
@@ -823,7 +845,11 @@ __global__ __launch_bounds__(kSegThreads) void k_sample_seg(SampleParams p) {
         // the waves before this one, in id order
         const int gw = seg * kSegWaves + wave;
         unsigned long long run = 0;
-        for (int w = 0; w < gw; ++w) run += WM[w];
+        for (int w = lane; w < gw; w += 64) run += WM[w];
+        for (int o = 32; o > 0; o >>= 1) {
+            const uint32_t lo = __shfl_xor((uint32_t)run, o), hi = __shfl_xor((uint32_t)(run >> 32), o);
+            run += ((unsigned long long)hi << 32) | lo;
+        }
         const unsigned long long wm = WM[gw];
         if (wm == 0 || tsel < run || tsel >= run + wm) return;
         for (int t = 0; t < nt; ++t) {

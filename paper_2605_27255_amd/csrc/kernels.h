@@ -127,6 +127,10 @@ struct GateParams {
     int V;
 };
 void launch_gate(const GateParams &p, hipStream_t s);
+// n0 words, then n1 and n2 floats (multiples of 4, 16-byte aligned), device to
+// device on one GPU; n1 and n2 may be 0.
+void launch_copy_out(void *d0, const void *s0, int n0, float *d1, const float *s1, int64_t n1, float *d2,
+                     const float *s2, int64_t n2, hipStream_t s);
 
 // Regular decoding (no compressor, one token per position and step).
 void launch_embed_step(const int32_t *pairs, const uint16_t *embed, int H, int V, float *x, float *ss, int B,

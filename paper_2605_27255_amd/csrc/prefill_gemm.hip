@@ -424,7 +424,7 @@ static GemmPlan gemm_plan(const GemmParams &p) {
     struct Shape { int rows, toks; double us; };
     static const Shape shapes[4] = {{256, 128, 0.78}, {128, 128, 0.48}, {128, 64, 0.25}, {128, 32, 0.21}};
     constexpr int kCU = 256, kMinTiles = 16;      // k tiles a range keeps at least
-    constexpr double kPartBytesPerUs = 6e6;
+    constexpr double kPartBytesPerUs = 4.5e6;
     const double fin_us = p.ss_in ? 9.0 : 5.0;    // (with the RMSNorm scale to form)
     const int KT = p.K >> 5;
     GemmPlan best{1, 0, 1};

@@ -729,12 +729,34 @@ static int check_sampling(pipo_ctx *c, const pipo_sampling *smp, int batch) {
     return PIPO_OK;
 }
 
-static int copy_outputs(pipo_ctx *c, pipo_pair *d_out, float *d_lb, float *d_ld, hipStream_t s) {
-    const int B = c->batch;
-    HIP_TRY(c, hipMemcpyAsync(d_out, c->out, sizeof(pipo_pair) * B, hipMemcpyDeviceToDevice, s));
-    if (d_lb) HIP_TRY(c, hipMemcpyAsync(d_lb, c->logits_b, sizeof(float) * B * c->V, hipMemcpyDeviceToDevice, s));
-    if (d_ld) HIP_TRY(c, hipMemcpyAsync(d_ld, c->logits_d, sizeof(float) * B * c->V, hipMemcpyDeviceToDevice, s));
+// Whether a kernel on the context's GPU may write at p in `align`-byte pieces.
+static bool writable_here(const pipo_ctx *c, const void *p, size_t align) {
+    hipPointerAttribute_t at;
+    if ((size_t)p % align) return false;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();   // unknown memory: the copies decide
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && at.device == c->dev;
+}
+
+// A step's results into the caller's buffers: one launch (a copy each cost
+// about 2 us of a step), or copies where a kernel cannot write there.
+static int copy_results(pipo_ctx *c, void *d0, const void *s0, int bytes, float *d_lb, float *d_ld, hipStream_t s) {
+    const int64_t n = (int64_t)c->batch * c->V;
+    if (writable_here(c, d0, 4) && (!d_lb || writable_here(c, d_lb, 16)) && (!d_ld || writable_here(c, d_ld, 16))) {
+        launch_copy_out(d0, s0, bytes / 4, d_lb, c->logits_b, d_lb ? n : 0, d_ld, c->logits_d, d_ld ? n : 0, s);
+        HIP_TRY(c, hipGetLastError());
+        return PIPO_OK;
+    }
+    HIP_TRY(c, hipMemcpyAsync(d0, s0, bytes, hipMemcpyDeviceToDevice, s));
+    if (d_lb) HIP_TRY(c, hipMemcpyAsync(d_lb, c->logits_b, sizeof(float) * n, hipMemcpyDeviceToDevice, s));
+    if (d_ld) HIP_TRY(c, hipMemcpyAsync(d_ld, c->logits_d, sizeof(float) * n, hipMemcpyDeviceToDevice, s));
     return PIPO_OK;
+}
+
+static int copy_outputs(pipo_ctx *c, pipo_pair *d_out, float *d_lb, float *d_ld, hipStream_t s) {
+    return copy_results(c, d_out, c->out, (int)sizeof(pipo_pair) * c->batch, d_lb, d_ld, s);
 }
 
 // The prompt prefill shared by both decoders: validation, sampling state,
@@ -959,10 +981,7 @@ static void enqueue_regular_decode(pipo_ctx *c, hipStream_t s) {
 }
 
 static int copy_tokens(pipo_ctx *c, int32_t *d_tok, float *d_logits, hipStream_t s) {
-    const int B = c->batch;
-    HIP_TRY(c, hipMemcpyAsync(d_tok, c->out_tok, sizeof(int32_t) * B, hipMemcpyDeviceToDevice, s));
-    if (d_logits) HIP_TRY(c, hipMemcpyAsync(d_logits, c->logits_b, sizeof(float) * B * c->V, hipMemcpyDeviceToDevice, s));
-    return PIPO_OK;
+    return copy_results(c, d_tok, c->out_tok, (int)sizeof(int32_t) * c->batch, d_logits, nullptr, s);
 }
 
 static int prefill_regular(pipo_ctx *c, int32_t batch, const int32_t *d_tokens, int32_t n, const int32_t *lens,
