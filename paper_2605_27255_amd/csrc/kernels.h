@@ -199,17 +199,38 @@ void launch_copy_bytes(void *dst, const void *src, int64_t n, hipStream_t s);
 struct PrefillGeom {
     int B;           // sequences
     int c0, clen;    // chunk start latent and latents in this chunk (the longest sequence's)
-    int mpad;        // per-sequence row stride (clen rounded up to 16)
+    int mpad;        // clen rounded up to 32: a sequence's rows in a uniform chunk, and in the query array
+    int M;           // rows in all (a multiple of 32)
     int n_tok;       // row stride of the token array, and every prompt's length when ntok is NULL
     const int32_t *ntok;   // per-sequence prompt lengths [B] (ragged batch), or NULL
     int tok_per_pos;       // prompt tokens per position: 2 (pairs), 1 (regular decoding)
+    // a ragged batch: each sequence has the rows of its own positions in the chunk (rounded up to
+    // 32, none once its prompt has ended), back to back; sequence b's start at row0[b], and 32-row
+    // block k holds rows 32 (blk[k] & 0xFFFF) .. of sequence blk[k] >> 16 (launch_row_map)
+    const int32_t *row0, *blk;
 };
+// Sequence b and position c0 + i of row m, and back.
+__device__ __forceinline__ void row_seq(const PrefillGeom &g, int m, int &b, int &i) {
+    if (g.blk) {
+        const int e = g.blk[m >> 5];
+        b = e >> 16;
+        i = ((e & 0xFFFF) << 5) + (m & 31);
+    } else {
+        b = m / g.mpad;
+        i = m - b * g.mpad;
+    }
+}
+__device__ __forceinline__ int row_of(const PrefillGeom &g, int b, int i) {
+    return (g.blk ? g.row0[b] : b * g.mpad) + i;
+}
 // Prompt tokens of sequence b.
 __device__ __forceinline__ int seq_tokens(const PrefillGeom &g, int b) { return g.ntok ? g.ntok[b] : g.n_tok; }
 // ... and its prompt's positions.
 __device__ __forceinline__ int seq_positions(const PrefillGeom &g, int b) {
     return (seq_tokens(g, b) + g.tok_per_pos - 1) / g.tok_per_pos;
 }
+// row0 and blk of a ragged chunk from its prompt lengths
+void launch_row_map(const PrefillGeom &g, int32_t *row0, int32_t *blk, hipStream_t s);
 void launch_gather_pairs(const int32_t *tokens, const uint16_t *embed, int H, int V, int pad_id,
                          const PrefillGeom &g, uint16_t *xin, hipStream_t s);
 void launch_gather_pair_sum(const int32_t *tokens, const uint16_t *embed, int H, int V, int pad_id,
@@ -257,7 +278,7 @@ struct AttnPrefillParams {
     uint16_t *kh, *vh;
     PrefillGeom g;
     int n_q, n_kv, d, lmax_pad;
-    uint16_t *out_hi, *out_lo;  // tiled [B*mpad][n_q*d], hi and lo planes
+    uint16_t *out_hi, *out_lo;  // tiled [M][n_q*d], hi and lo planes
 };
 void launch_attn_prefill(const AttnPrefillParams &p, hipStream_t s);
 // After a chunk: every sequence whose last position (ceil(n_b / 2) - 1, or

@@ -8,16 +8,35 @@
 
 namespace pipo {
 
+// ---- rows of a ragged chunk (one wave; lane b: sequence b, up to 64) -------
+__global__ __launch_bounds__(64) void k_row_map(PrefillGeom g, int32_t *row0, int32_t *blk) {
+    const int b = threadIdx.x;
+    const int n = b < g.B ? min(max(seq_positions(g, b) - g.c0, 0), g.clen) : 0;
+    const int nb = (n + 31) >> 5;
+    int end = nb;
+    for (int d = 1; d < 64; d <<= 1) {
+        const int y = __shfl_up(end, d);
+        if (b >= d) end += y;
+    }
+    if (b < g.B) row0[b] = (end - nb) * 32;
+    for (int k = 0; k < nb; ++k) blk[end - nb + k] = (b << 16) | k;
+}
+
+void launch_row_map(const PrefillGeom &g, int32_t *row0, int32_t *blk, hipStream_t s) {
+    hipLaunchKernelGGL(k_row_map, dim3(1), dim3(64), 0, s, g, row0, blk);
+}
+
 // ---- pair gather: X_in[m] = [E[a]; E[b]] for latent c0 + i of sequence b ----
 __global__ void k_gather_pairs(const int32_t *tokens, const uint16_t *embed, int H, int V, int pad_id,
                                PrefillGeom g, uint16_t *xin) {
     const int cpr = (2 * H) >> 3;
-    const int64_t total = (int64_t)g.B * g.mpad * cpr;
+    const int64_t total = (int64_t)g.M * cpr;
     for (int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; idx < total;
          idx += (int64_t)gridDim.x * blockDim.x) {
         const int m = (int)(idx / cpr);
         const int k = (int)(idx - (int64_t)m * cpr) << 3;
-        const int b = m / g.mpad, i = m - b * g.mpad;
+        int b, i;
+        row_seq(g, m, b, i);
         int row = pad_id;
         if (i < g.clen) {   // rows past a sequence's prompt (ragged batch) hold (PAD, PAD)
             const int t = 2 * (g.c0 + i) + (k < H ? 0 : 1);
@@ -30,7 +49,7 @@ __global__ void k_gather_pairs(const int32_t *tokens, const uint16_t *embed, int
 
 void launch_gather_pairs(const int32_t *tokens, const uint16_t *embed, int H, int V, int pad_id,
                          const PrefillGeom &g, uint16_t *xin, hipStream_t s) {
-    const int64_t total = (int64_t)g.B * g.mpad * ((2 * H) >> 3);
+    const int64_t total = (int64_t)g.M * ((2 * H) >> 3);
     int grid = (int)((total + 255) / 256);
     grid = grid > 65536 ? 65536 : grid;
     hipLaunchKernelGGL(k_gather_pairs, dim3(grid), dim3(256), 0, s, tokens, embed, H, V, pad_id, g, xin);
@@ -40,12 +59,13 @@ void launch_gather_pairs(const int32_t *tokens, const uint16_t *embed, int H, in
 __global__ void k_gather_pair_sum(const int32_t *tokens, const uint16_t *embed, int H, int V, int pad_id,
                                   PrefillGeom g, float *x) {
     const int cpr = H >> 3;
-    const int64_t total = (int64_t)g.B * g.mpad * cpr;
+    const int64_t total = (int64_t)g.M * cpr;
     for (int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; idx < total;
          idx += (int64_t)gridDim.x * blockDim.x) {
         const int m = (int)(idx / cpr);
         const int k = (int)(idx - (int64_t)m * cpr) << 3;
-        const int b = m / g.mpad, i = m - b * g.mpad;
+        int b, i;
+        row_seq(g, m, b, i);
         int ra = pad_id, rb = pad_id;
         if (i < g.clen) {
             const int t = 2 * (g.c0 + i), nb = seq_tokens(g, b);
@@ -64,7 +84,7 @@ __global__ void k_gather_pair_sum(const int32_t *tokens, const uint16_t *embed, 
 
 void launch_gather_pair_sum(const int32_t *tokens, const uint16_t *embed, int H, int V, int pad_id,
                             const PrefillGeom &g, float *x, hipStream_t s) {
-    const int64_t total = (int64_t)g.B * g.mpad * (H >> 3);
+    const int64_t total = (int64_t)g.M * (H >> 3);
     int grid = (int)((total + 255) / 256);
     grid = grid > 65536 ? 65536 : grid;
     hipLaunchKernelGGL(k_gather_pair_sum, dim3(grid), dim3(256), 0, s, tokens, embed, H, V, pad_id, g, x);
@@ -81,7 +101,8 @@ __global__ __launch_bounds__(256) void k_mtp_rows(const float *xb, const int32_t
     const int lane = threadIdx.x & 63;
     const int m = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (m >= M) return;
-    const int b = m / g.mpad, i = m - b * g.mpad;
+    int b, i;
+    row_seq(g, m, b, i);
     const int t = 2 * (g.c0 + i) + 2;
     const int tok = (i < g.clen && t < seq_tokens(g, b)) ? clamp_id(tokens[(int64_t)b * g.n_tok + t], V) : pad_id;
     const float *xr = xb + (int64_t)m * H;
@@ -128,16 +149,17 @@ void launch_mtp_rows(const float *xb, const int32_t *tokens, const uint16_t *emb
 
 // ---- regular decoding: the prompt's tokens one per position, x = E[t] -----
 // Row (b, i) of the chunk holds token c0 + i of sequence b (rows past the
-// chunk hold E[pad_id]); fp32 residual rows [B * mpad][H].
+// chunk hold E[pad_id]); fp32 residual rows [M][H].
 __global__ void k_gather_tokens(const int32_t *tokens, const uint16_t *embed, int H, int V, int pad_id,
                                 PrefillGeom g, float *x) {
     const int cpr = H >> 3;
-    const int64_t total = (int64_t)g.B * g.mpad * cpr;
+    const int64_t total = (int64_t)g.M * cpr;
     for (int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; idx < total;
          idx += (int64_t)gridDim.x * blockDim.x) {
         const int m = (int)(idx / cpr);
         const int k = (int)(idx - (int64_t)m * cpr) << 3;
-        const int b = m / g.mpad, i = m - b * g.mpad;
+        int b, i;
+        row_seq(g, m, b, i);
         const int t = g.c0 + i;
         const int row = (i < g.clen && t < seq_tokens(g, b)) ? clamp_id(tokens[(int64_t)b * g.n_tok + t], V) : pad_id;
         const u32x4 v = *(const u32x4 *)(embed + tiled_index(row, k, H));
@@ -149,7 +171,7 @@ __global__ void k_gather_tokens(const int32_t *tokens, const uint16_t *embed, in
 
 void launch_gather_tokens(const int32_t *tokens, const uint16_t *embed, int H, int V, int pad_id,
                           const PrefillGeom &g, float *x, hipStream_t s) {
-    const int64_t total = (int64_t)g.B * g.mpad * (H >> 3);
+    const int64_t total = (int64_t)g.M * (H >> 3);
     int grid = (int)((total + 255) / 256);
     grid = grid > 65536 ? 65536 : grid;
     hipLaunchKernelGGL(k_gather_tokens, dim3(grid), dim3(256), 0, s, tokens, embed, H, V, pad_id, g, x);
@@ -264,7 +286,7 @@ __global__ __launch_bounds__(256) void k_pick_last(const float *x, int H, Prefil
     const int nb = seq_tokens(g, b);
     const int last = (regular ? nb : (nb + 1) / 2) - 1;   // the sequence's last position
     if (last < g.c0 || last >= g.c0 + g.clen) return;
-    const float *xr = x + ((int64_t)b * g.mpad + last - g.c0) * H;
+    const float *xr = x + (int64_t)row_of(g, b, last - g.c0) * H;
     for (int k = threadIdx.x; k < H; k += 256) xdec[(int64_t)b * H + k] = xr[k];
     for (int st = threadIdx.x; st < (H >> 4); st += 256) {
         float a = 0.f;

@@ -188,10 +188,11 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(AttnPrefillParams p) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no load to LDS outlives the workgroup
     const int i = q0 + j;
     l_run += __shfl_xor(l_run, 32);
-    if (!active || i >= p.g.clen) return;
+    // (a ragged batch: rows past this sequence's positions are another's)
+    if (!active || i >= p.g.clen || (p.g.ntok && p.g.c0 + i >= seq_positions(p.g, b))) return;
     const float inv = 1.0f / l_run;
     const int qd = p.n_q * D;
-    const int64_t m = (int64_t)b * p.g.mpad + i;
+    const int64_t m = row_of(p.g, b, i);
 #pragma unroll
     for (int t = 0; t < ND; ++t)
 #pragma unroll

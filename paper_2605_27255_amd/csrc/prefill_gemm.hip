@@ -30,12 +30,10 @@ __device__ __forceinline__ void gemm_epi(const GemmParams &p, f32x4 a, f32x4 c, 
         i = 0;
         pos = EPI == EPI_QKV ? p.dpos[m] : 0;
     } else {
-        b = m / p.g.mpad;
-        i = m - b * p.g.mpad;
+        row_seq(p.g, m, b, i);
         pos = p.g.c0 + i;
-        // Rows past the chunk or past a ragged batch's shorter prompt hold nothing:
-        // their X may be stale (a tile of another shape was skipped there), and the
-        // cache keeps finite values at positions no prompt has reached.
+        // rows that pad a sequence to 32 hold nothing; the cache keeps finite
+        // values at positions no prompt has reached
         if (i >= p.g.clen || (p.g.ntok && pos >= seq_positions(p.g, b))) return;
     }
     const int row0 = strip * 16 + 4 * h;
@@ -204,19 +202,6 @@ __device__ __forceinline__ void tile_of(int u, int nbn, int nbm, int &bn, int &b
     bm = r / gs;
 }
 
-// A ragged batch: a token tile of which no row is a sequence's position holds
-// only PAD rows, whose outputs nothing reads.
-__device__ __forceinline__ bool pad_rows(const GemmParams &p, int m0, int m1) {
-    if (!p.g.ntok) return false;
-    m1 = min(m1, p.M);
-    bool any = false;
-    for (int sb = m0 / p.g.mpad; sb * p.g.mpad < m1; ++sb) {
-        const int i0 = max(m0 - sb * p.g.mpad, 0);
-        any = any || p.g.c0 + i0 < seq_positions(p.g, sb);
-    }
-    return !any;
-}
-
 template <int EPI, bool HASLO, class TL>
 __global__ __launch_bounds__(256, TL::MINW) void k_gemm(GemmParams p) {
     constexpr int NR = TL::NR, NT = TL::NT, WT = TL::WT, S = TL::S;
@@ -238,7 +223,6 @@ __global__ __launch_bounds__(256, TL::MINW) void k_gemm(GemmParams p) {
     const int range = part ? u / (T - full) : 0, pt = part ? u - range * (T - full) : 0;
     int bn, bm;
     tile_of(part ? full + pt : u, nbn, nbm, bn, bm);
-    if (pad_rows(p, bm * TL::TOKS, (bm + 1) * TL::TOKS)) return;
     const int KT = p.K >> 5;
     const int kt0 = part ? (int)((int64_t)range * KT / p.ksplit) : 0;
     const int kt1 = part ? (int)((int64_t)(range + 1) * KT / p.ksplit) : KT;
@@ -362,7 +346,7 @@ __global__ __launch_bounds__(128) void k_gemm_fin(GemmParams p) {
     int bn, bm;
     tile_of(p.full + pt, nbn, nbm, bn, bm);
     const int strip = bn * (TL::ROWS / 16) + 2 * rb + t, m0 = bm * TL::TOKS + tb * 32;
-    if (strip >= (p.N >> 4) || m0 >= p.M || pad_rows(p, m0, m0 + 32)) return;
+    if (strip >= (p.N >> 4) || m0 >= p.M) return;
     const float *src = p.part + (int64_t)blockIdx.x * 1024 + 512 * t + lane * 4;
     const int64_t stride = (int64_t)gridDim.x * 1024;
     f32x4 a = f32x4{0.f, 0.f, 0.f, 0.f}, c = a;

@@ -90,6 +90,7 @@ struct pipo_ctx {
     hipEvent_t seeds_done = nullptr;
     int32_t *h_lens = nullptr;       // pinned staging for the prompt lengths of a ragged batch
     hipEvent_t lens_done = nullptr;
+    int32_t *row0 = nullptr, *row_blk = nullptr;   // device: rows of a ragged chunk (PrefillGeom)
     int32_t *ntok = nullptr;         // device: prompt lengths of the last ragged prefill [Bmax]
     hipStream_t cap_stream = nullptr;
 
@@ -313,7 +314,7 @@ extern "C" int pipo_init_weights(const pipo_config *cfg, uint64_t seed, void *st
 
     // ---- KV cache, RoPE table, activations ------------------------------
     Arena a;
-    const int64_t mcap = (int64_t)B * round_up(c->chunk, 64);   // rows per chunk: ragged batches pad to 64
+    const int64_t mcap = (int64_t)B * round_up(c->chunk, 64);   // rows per chunk
     const int S_att = 64;
     for (int pass = 0; pass < 2; ++pass) {
         a.used = 0;
@@ -349,6 +350,8 @@ extern "C" int pipo_init_weights(const pipo_config *cfg, uint64_t seed, void *st
         c->seeds = a.take<uint64_t>(B);
         c->pairs = a.take<int32_t>(2 * B);
         c->ntok = a.take<int32_t>(B);
+        c->row0 = a.take<int32_t>(B);
+        c->row_blk = a.take<int32_t>(mcap / 32);
         c->seen_words = (V + 31) / 32;
         c->seen = a.take<uint32_t>((int64_t)B * c->seen_words);
         c->pen = a.take<float>((int64_t)B * V);
@@ -833,10 +836,19 @@ static int prefill_backbone(pipo_ctx *c, int32_t batch, const int32_t *d_tokens,
     PrefillGeom g{};
     for (int c0 = 0; c0 < positions; c0 += c->chunk) {
         g.B = batch; g.c0 = c0; g.clen = std::min(c->chunk, positions - c0);
-        // ragged batches pad each sequence's rows to whole 64-row GEMM tiles, so
-        // that tiles past a shorter prompt can be skipped
-        g.mpad = (int)round_up(g.clen, ntok ? 64 : 32); g.n_tok = n; g.ntok = ntok; g.tok_per_pos = regular ? 1 : 2;
-        const int M = batch * g.mpad;
+        g.mpad = (int)round_up(g.clen, 32); g.n_tok = n; g.ntok = ntok; g.tok_per_pos = regular ? 1 : 2;
+        g.M = batch * g.mpad;
+        if (ntok) {   // each sequence's own positions, back to back
+            g.M = 0;
+            for (int b = 0; b < batch; ++b) {
+                const int pos_b = regular ? lens[b] : (lens[b] + 1) / 2;
+                g.M += (int)round_up(std::min(std::max(pos_b - c0, 0), g.clen), 32);
+            }
+            g.row0 = c->row0; g.blk = c->row_blk;
+            PROF(PIPO_K_PREFILL_MISC);
+            launch_row_map(g, c->row0, c->row_blk, s);
+        }
+        const int M = g.M;
         GemmParams gp{};
         gp.g = g; gp.M = M;
         gp.n_q = c->nq; gp.n_kv = c->nkv; gp.d = c->d; gp.lmax_pad = c->lmax_pad; gp.kv_bstride = c->kv_bstride;
