@@ -23,10 +23,12 @@
 
 namespace pipo {
 
-// Output element (row b, column c), as the next kernel takes it.
+// Output element (row b, column c), as the next kernel takes it (PL: as hi and
+// lo planes; a template argument, so that the fp32 form has no branch).
+template <bool PL>
 __device__ __forceinline__ void put_out(const AttnDecodeParams &p, int b, int c, int D, float v) {
     const int qd = p.n_q * D;
-    if (p.out_hi) {
+    if constexpr (PL) {
         uint32_t hi, lo;
         split_bf(v, hi, lo);
         const int64_t at = tiled_index(b, c, qd);
@@ -42,7 +44,7 @@ __device__ __forceinline__ void put_out(const AttnDecodeParams &p, int b, int c,
 // D / 16 dimensions each, four heads at a time; the splits go in split order,
 // XU at a time, with the running maximum M and the sums L and o rescaled by
 // exp2(M_old - M_new) as it rises; then o / L.
-template <int D>
+template <int D, bool PL>
 __device__ void xl_merge(const AttnDecodeParams &p, int b, int kvh, int qpg, int S, int lane) {
     constexpr int RS = attn_part_stride(D), DPL = D / 16, XU = 12;
     const float *rec = p.part + ((int64_t)b * p.n_q + kvh * qpg) * S * RS;   // [qpg][S][RS]
@@ -86,9 +88,9 @@ __device__ void xl_merge(const AttnDecodeParams &p, int b, int kvh, int qpg, int
         }
         if (hj < qpg) {
             const float inv = 1.0f / L;
-            if (p.out_hi) {
+            if constexpr (PL) {
 #pragma unroll
-                for (int k = 0; k < DPL; ++k) put_out(p, b, (kvh * qpg + hj) * D + d0 + k, D, acc[k] * inv);
+                for (int k = 0; k < DPL; ++k) put_out<PL>(p, b, (kvh * qpg + hj) * D + d0 + k, D, acc[k] * inv);
             } else {
                 float *o = p.out + ((int64_t)b * p.n_q + kvh * qpg + hj) * D + d0;
 #pragma unroll
@@ -115,7 +117,7 @@ __device__ void xl_merge(const AttnDecodeParams &p, int b, int kvh, int qpg, int
 // the workgroup writes the output rows.  At most 256 registers a lane, so
 // that two waves fit on a SIMD (9B at batch 8: 2.86 ms of attention per pair
 // step this way, 2.88 with the 278 the compiler chooses otherwise).
-template <int D, bool FUSED, int NW>
+template <int D, bool FUSED, int NW, bool PL>
 __global__ __launch_bounds__(64 * NW, 2) void k_attn_decode(AttnDecodeParams p) {
     constexpr int NC = D / 32;   // 32-wide d chunks (QK^T k-steps)
     constexpr int NT = D / 16;   // 16-wide d tiles (PV output tiles)
@@ -430,7 +432,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attn_decode(AttnDecodeParams p) 
             old = __builtin_amdgcn_readfirstlane(old);
             if (old == S - 1) {
                 if (lane == 0) __hip_atomic_store(p.xl_ctr + bk, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                xl_merge<D>(p, b, kvh, qpg, S, lane);
+                xl_merge<D, PL>(p, b, kvh, qpg, S, lane);
             }
         }
     } else {
@@ -462,7 +464,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attn_decode(AttnDecodeParams p) 
                 L += ww * red[w][hj][D + 1];
                 acc += ww * red[w][hj][dim];
             }
-            put_out(p, b, (kvh * qpg + hj) * D + dim, D, acc * (1.0f / L));
+            put_out<PL>(p, b, (kvh * qpg + hj) * D + dim, D, acc * (1.0f / L));
         }
     }
 }
@@ -471,7 +473,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attn_decode(AttnDecodeParams p) 
 // owns dimension t.  Weights exp2(m_s - M) and L = sum_s w_s l_s, then the
 // weighted sum of the split outputs in split order; every split's value is
 // requested before any is used.
-template <int D>
+template <int D, bool PL>
 __global__ __launch_bounds__(D) void k_attn_merge(AttnDecodeParams p) {
     constexpr int SMAX = 64;
     __shared__ float s_w[SMAX];
@@ -499,7 +501,7 @@ __global__ __launch_bounds__(D) void k_attn_merge(AttnDecodeParams p) {
 #pragma unroll
     for (int sp = 0; sp < SMAX; ++sp) acc += sp < S ? s_w[sp] * ov[sp] : 0.f;
     const int b = bh / p.n_q;
-    put_out(p, b, (bh - b * p.n_q) * D + t, D, acc * s_inv);
+    put_out<PL>(p, b, (bh - b * p.n_q) * D + t, D, acc * s_inv);
 }
 
 __global__ __launch_bounds__(64) void k_xcd_probe(int *out) {
@@ -533,32 +535,31 @@ hipError_t probe_xcd_round_robin(hipStream_t s, bool *ok) {
     return hipSuccess;
 }
 
-void launch_attn_decode(const AttnDecodeParams &p, hipStream_t s) {
-    const bool fused = p.qkv_part != nullptr;
+template <int D, bool FUSED, bool PL>
+static void launch_attn_decode_t(const AttnDecodeParams &p, hipStream_t s) {
     if (p.splits == kAttnWgSplits) {   // one workgroup per (sequence, KV group), no merge launch
-        const int grid = p.B * p.n_kv;
         constexpr int NW = kAttnWgSplits;
-        if (p.d == 128) {
-            if (fused) hipLaunchKernelGGL((k_attn_decode<128, true, NW>), dim3(grid), dim3(64 * NW), 0, s, p);
-            else hipLaunchKernelGGL((k_attn_decode<128, false, NW>), dim3(grid), dim3(64 * NW), 0, s, p);
-        } else {
-            if (fused) hipLaunchKernelGGL((k_attn_decode<64, true, NW>), dim3(grid), dim3(64 * NW), 0, s, p);
-            else hipLaunchKernelGGL((k_attn_decode<64, false, NW>), dim3(grid), dim3(64 * NW), 0, s, p);
-        }
+        hipLaunchKernelGGL((k_attn_decode<D, FUSED, NW, PL>), dim3(p.B * p.n_kv), dim3(64 * NW), 0, s, p);
         return;
     }
     const bool xl = p.xl_ctr != nullptr;
     const int pairs = p.B * p.n_kv;
     const int grid = xl ? 8 * p.splits * ((pairs + 7) / 8) : pairs * p.splits;
-    if (p.d == 128) {
-        if (fused) hipLaunchKernelGGL((k_attn_decode<128, true, 1>), dim3(grid), dim3(64), 0, s, p);
-        else hipLaunchKernelGGL((k_attn_decode<128, false, 1>), dim3(grid), dim3(64), 0, s, p);
-        if (!xl) hipLaunchKernelGGL(k_attn_merge<128>, dim3(p.B * p.n_q), dim3(128), 0, s, p);
-    } else {
-        if (fused) hipLaunchKernelGGL((k_attn_decode<64, true, 1>), dim3(grid), dim3(64), 0, s, p);
-        else hipLaunchKernelGGL((k_attn_decode<64, false, 1>), dim3(grid), dim3(64), 0, s, p);
-        if (!xl) hipLaunchKernelGGL(k_attn_merge<64>, dim3(p.B * p.n_q), dim3(64), 0, s, p);
-    }
+    hipLaunchKernelGGL((k_attn_decode<D, FUSED, 1, PL>), dim3(grid), dim3(64), 0, s, p);
+    if (!xl) hipLaunchKernelGGL((k_attn_merge<D, PL>), dim3(p.B * p.n_q), dim3(D), 0, s, p);
+}
+
+template <int D>
+static void launch_attn_decode_d(const AttnDecodeParams &p, hipStream_t s) {
+    // (the tiled GEMM, which takes planes, finishes QKV itself)
+    if (p.out_hi) launch_attn_decode_t<D, false, true>(p, s);
+    else if (p.qkv_part) launch_attn_decode_t<D, true, false>(p, s);
+    else launch_attn_decode_t<D, false, false>(p, s);
+}
+
+void launch_attn_decode(const AttnDecodeParams &p, hipStream_t s) {
+    if (p.d == 128) launch_attn_decode_d<128>(p, s);
+    else launch_attn_decode_d<64>(p, s);
 }
 
 }  // namespace pipo
