@@ -334,7 +334,9 @@ extern "C" int pipo_init_weights(const pipo_config *cfg, uint64_t seed, void *st
         c->logits_d = a.take<float>((int64_t)B * V);
         c->qbuf = a.take<float>((int64_t)B * c->qdim);
         c->attn_out = a.take<float>((int64_t)B * c->qdim);
-        c->act = a.take<float>((int64_t)B * F);
+        // besides the F-wide activation: the MLP compressor's and confidence head's H-wide hidden rows ...
+        const int64_t act_w = c->heads & (PIPO_HEADS_MLP_COMPRESSOR | PIPO_HEADS_MLP_CONFIDENCE) ? std::max(F, H) : F;
+        c->act = a.take<float>(B * act_w);
         {
             const int64_t kmax = std::max<int64_t>(std::max<int64_t>(2 * H, F), c->qdim);
             c->xh = a.take<uint16_t>((int64_t)B * kmax);
@@ -377,8 +379,11 @@ extern "C" int pipo_init_weights(const pipo_config *cfg, uint64_t seed, void *st
         c->p_vh = a.take<uint16_t>((int64_t)B * c->kv_bstride);
         c->p_o = a.take<uint16_t>(mcap * c->qdim);
         c->p_o_lo = a.take<uint16_t>(mcap * c->qdim);
-        c->p_act = a.take<uint16_t>(mcap * F);
-        c->p_act_lo = a.take<uint16_t>(mcap * F);
+        // ... and, of a chunk, the compressor's H-wide rows and the MTP projection's 2H-wide inputs
+        const int64_t p_act_w = std::max<int64_t>(F, c->heads & PIPO_HEADS_MTP_LAYER ? 2 * H
+                                                     : c->heads & PIPO_HEADS_MLP_COMPRESSOR ? H : 0);
+        c->p_act = a.take<uint16_t>(mcap * p_act_w);
+        c->p_act_lo = a.take<uint16_t>(mcap * p_act_w);
         // two rounds of 256 x 128 tiles over the CUs, or 16 ranges of the widest output if that is less
         c->p_part_cap = std::min<int64_t>((int64_t)16 << 20, 16 * round_up(mcap, 128) *
                                           round_up(std::max<int64_t>(2 * F, c->nqkv), 256));

@@ -552,6 +552,24 @@ def test_4b_width_paper_heads(torch):
         m.close()
 
 
+@pytest.mark.parametrize("hidden,nq,nkv,d,ffn", [(96, 3, 1, 128, 160), (256, 4, 2, 64, 96)])
+@pytest.mark.parametrize("heads", [1, 2, 4, 7])
+def test_paper_heads_wider_than_the_ffn(torch, hidden, nq, nkv, d, ffn, heads):
+    """ffn < 2 hidden, and ffn < hidden, with every row of two full chunks in
+    use: the MTP projection's 2 hidden-wide inputs and the MLP heads' hidden-wide
+    activations are wider than the FFN's, and the MTP keys and values they give
+    are read by the steps that follow."""
+    cfg = ModelConfig(n_layers=1, hidden=hidden, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, ffn=ffn, vocab=1008,
+                      rope_base=1e4, heads=heads)
+    B, n, steps = 8, 256, 2
+    prompts = rspec.prompt_tokens(B, n, cfg.vocab, seed=24)
+    m = _model(cfg, seed=16, max_batch=B, max_latent=n // 2 + steps + 1, prefill_chunk=64)
+    W = O.OracleWeights.generate(cfg, seed=16, precision="bf16")
+    rep, _ = run_parity(m, W, prompts, steps, O.Sampling(tau=0.5), log)
+    rep.check()
+    m.close()
+
+
 # ------------------------------------------------------------ edge cases
 
 def test_tiny_degenerate_and_tile_boundary_prompts(torch):
