@@ -737,29 +737,35 @@ static int check_sampling(pipo_ctx *c, const pipo_sampling *smp, int batch) {
     return PIPO_OK;
 }
 
-// Whether a kernel on the context's GPU may write at p in `align`-byte pieces.
-static bool writable_here(const pipo_ctx *c, const void *p, size_t align) {
+// Whether a kernel on the context's GPU may write `bytes` bytes at p in
+// `align`-byte pieces: its own device memory, all of it inside one allocation.
+static bool writable_here(const pipo_ctx *c, void *p, size_t bytes, size_t align) {
     hipPointerAttribute_t at;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
     if ((size_t)p % align) return false;
-    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+    if (hipPointerGetAttributes(&at, p) != hipSuccess || hipMemGetAddressRange(&base, &size, p) != hipSuccess) {
         (void)hipGetLastError();   // unknown memory: the copies decide
         return false;
     }
-    return at.type == hipMemoryTypeDevice && at.device == c->dev;
+    return at.type == hipMemoryTypeDevice && at.device == c->dev && (size_t)((char *)p - (char *)base) + bytes <= size;
 }
 
 // A step's results into the caller's buffers: one launch (a copy each cost
-// about 2 us of a step), or copies where a kernel cannot write there.
+// about 2 us of a step), or copies where a kernel cannot write there (which
+// refuse a buffer that ends too early).
 static int copy_results(pipo_ctx *c, void *d0, const void *s0, int bytes, float *d_lb, float *d_ld, hipStream_t s) {
     const int64_t n = (int64_t)c->batch * c->V;
-    if (writable_here(c, d0, 4) && (!d_lb || writable_here(c, d_lb, 16)) && (!d_ld || writable_here(c, d_ld, 16))) {
+    const size_t lbytes = sizeof(float) * (size_t)n;
+    if (writable_here(c, d0, bytes, 4) && (!d_lb || writable_here(c, d_lb, lbytes, 16)) &&
+        (!d_ld || writable_here(c, d_ld, lbytes, 16))) {
         launch_copy_out(d0, s0, bytes / 4, d_lb, c->logits_b, d_lb ? n : 0, d_ld, c->logits_d, d_ld ? n : 0, s);
         HIP_TRY(c, hipGetLastError());
         return PIPO_OK;
     }
     HIP_TRY(c, hipMemcpyAsync(d0, s0, bytes, hipMemcpyDeviceToDevice, s));
-    if (d_lb) HIP_TRY(c, hipMemcpyAsync(d_lb, c->logits_b, sizeof(float) * n, hipMemcpyDeviceToDevice, s));
-    if (d_ld) HIP_TRY(c, hipMemcpyAsync(d_ld, c->logits_d, sizeof(float) * n, hipMemcpyDeviceToDevice, s));
+    if (d_lb) HIP_TRY(c, hipMemcpyAsync(d_lb, c->logits_b, lbytes, hipMemcpyDeviceToDevice, s));
+    if (d_ld) HIP_TRY(c, hipMemcpyAsync(d_ld, c->logits_d, lbytes, hipMemcpyDeviceToDevice, s));
     return PIPO_OK;
 }
 
