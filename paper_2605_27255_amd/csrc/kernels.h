@@ -206,15 +206,21 @@ struct PrefillGeom {
     int tok_per_pos;       // prompt tokens per position: 2 (pairs), 1 (regular decoding)
     // a ragged batch: each sequence has the rows of its own positions in the chunk (rounded up to
     // 32, none once its prompt has ended), back to back; sequence b's start at row0[b], and 32-row
-    // block k holds rows 32 (blk[k] & 0xFFFF) .. of sequence blk[k] >> 16 (launch_row_map)
-    const int32_t *row0, *blk;
+    // block j holds the rows of the sequence and its block that blk[j] names (launch_row_map)
+    const int32_t *row0; const uint32_t *blk;
 };
+// A 32-row block of a ragged chunk: block k of sequence b in six and 26 bits
+// (64 sequences, and every block of 2^31 positions).
+constexpr int kRowBlockBits = 26;
+__host__ __device__ constexpr uint32_t row_block(int b, int k) { return (uint32_t)b << kRowBlockBits | (uint32_t)k; }
+__host__ __device__ constexpr int row_block_seq(uint32_t e) { return (int)(e >> kRowBlockBits); }
+__host__ __device__ constexpr int row_block_index(uint32_t e) { return (int)(e & ((1u << kRowBlockBits) - 1)); }
 // Sequence b and position c0 + i of row m, and back.
 __device__ __forceinline__ void row_seq(const PrefillGeom &g, int m, int &b, int &i) {
     if (g.blk) {
-        const int e = g.blk[m >> 5];
-        b = e >> 16;
-        i = ((e & 0xFFFF) << 5) + (m & 31);
+        const uint32_t e = g.blk[m >> 5];
+        b = row_block_seq(e);
+        i = (row_block_index(e) << 5) + (m & 31);
     } else {
         b = m / g.mpad;
         i = m - b * g.mpad;
@@ -230,7 +236,7 @@ __device__ __forceinline__ int seq_positions(const PrefillGeom &g, int b) {
     return (seq_tokens(g, b) + g.tok_per_pos - 1) / g.tok_per_pos;
 }
 // row0 and blk of a ragged chunk from its prompt lengths
-void launch_row_map(const PrefillGeom &g, int32_t *row0, int32_t *blk, hipStream_t s);
+void launch_row_map(const PrefillGeom &g, int32_t *row0, uint32_t *blk, hipStream_t s);
 void launch_gather_pairs(const int32_t *tokens, const uint16_t *embed, int H, int V, int pad_id,
                          const PrefillGeom &g, uint16_t *xin, hipStream_t s);
 void launch_gather_pair_sum(const int32_t *tokens, const uint16_t *embed, int H, int V, int pad_id,

@@ -9,7 +9,7 @@
 namespace pipo {
 
 // ---- rows of a ragged chunk (one wave; lane b: sequence b, up to 64) -------
-__global__ __launch_bounds__(64) void k_row_map(PrefillGeom g, int32_t *row0, int32_t *blk) {
+__global__ __launch_bounds__(64) void k_row_map(PrefillGeom g, int32_t *row0, uint32_t *blk) {
     const int b = threadIdx.x;
     const int n = b < g.B ? min(max(seq_positions(g, b) - g.c0, 0), g.clen) : 0;
     const int nb = (n + 31) >> 5;
@@ -19,10 +19,10 @@ __global__ __launch_bounds__(64) void k_row_map(PrefillGeom g, int32_t *row0, in
         if (b >= d) end += y;
     }
     if (b < g.B) row0[b] = (end - nb) * 32;
-    for (int k = 0; k < nb; ++k) blk[end - nb + k] = (b << 16) | k;
+    for (int k = 0; k < nb; ++k) blk[end - nb + k] = row_block(b, k);
 }
 
-void launch_row_map(const PrefillGeom &g, int32_t *row0, int32_t *blk, hipStream_t s) {
+void launch_row_map(const PrefillGeom &g, int32_t *row0, uint32_t *blk, hipStream_t s) {
     hipLaunchKernelGGL(k_row_map, dim3(1), dim3(64), 0, s, g, row0, blk);
 }
 

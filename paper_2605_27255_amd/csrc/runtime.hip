@@ -90,7 +90,7 @@ struct pipo_ctx {
     hipEvent_t seeds_done = nullptr;
     int32_t *h_lens = nullptr;       // pinned staging for the prompt lengths of a ragged batch
     hipEvent_t lens_done = nullptr;
-    int32_t *row0 = nullptr, *row_blk = nullptr;   // device: rows of a ragged chunk (PrefillGeom)
+    int32_t *row0 = nullptr; uint32_t *row_blk = nullptr;   // device: rows of a ragged chunk (PrefillGeom)
     int32_t *ntok = nullptr;         // device: prompt lengths of the last ragged prefill [Bmax]
     hipStream_t cap_stream = nullptr;
 
@@ -353,7 +353,7 @@ extern "C" int pipo_init_weights(const pipo_config *cfg, uint64_t seed, void *st
         c->pairs = a.take<int32_t>(2 * B);
         c->ntok = a.take<int32_t>(B);
         c->row0 = a.take<int32_t>(B);
-        c->row_blk = a.take<int32_t>(mcap / 32);
+        c->row_blk = a.take<uint32_t>(mcap / 32);
         c->seen_words = (V + 31) / 32;
         c->seen = a.take<uint32_t>((int64_t)B * c->seen_words);
         c->pen = a.take<float>((int64_t)B * V);
