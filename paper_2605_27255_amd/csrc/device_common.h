@@ -66,11 +66,16 @@ __device__ __forceinline__ uint32_t pack_f16x2(float lo, float hi) {
 // 16 bytes per lane from src + 16 lane (src uniform) to LDS byte address
 // lds + 16 lane.  Counted by vmcnt, which the compiler does not track here:
 // the caller waits for it explicitly.  (s_nop: one wait state between the
-// write of M0 and its use.)
+// write of M0 and its use.  M0 is declared as written, so that a value the
+// compiler put there itself is set anew; its warning that a reserved register
+// is not kept across the statement says the same.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void load_to_lds(const uint16_t *src, uint32_t lds, uint32_t lane16) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "s"(lds), "v"(lane16), "s"(src) : "memory");
+                 :: "s"(lds), "v"(lane16), "s"(src) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 
 // ---- wave reductions -------------------------------------------------------
 __device__ __forceinline__ float wave_sum(float v) {
