@@ -162,7 +162,7 @@ template <int NBT, int PRO, int EPI>
 struct Pro {
     static constexpr int RPW = 2 * NBT;    // RMSNorm rows per wave: b = wave + 8 r
     f32x4 resid[NBT];
-    float ssv[RPW][4];                     // sum-of-squares parts, 4 per lane (nss <= 256)
+    float ssv[RPW][4];                     // sum-of-squares parts, 4 per lane (nss <= kGemvSsParts)
     float ssv2[PRO == PRO_CAT ? RPW : 1][4];   // PRO_CAT: the second half's parts
     XSrc src[kXR];
 };
@@ -1190,6 +1190,17 @@ static int launch_nbt(const GemvParams &p, hipStream_t s) {
 }
 
 int gemv_num_groups(int N) { return N >> 4; }
+
+__global__ __launch_bounds__(kGemvSsParts) void k_ss_fold(const float *ss, int nss, float *out) {
+    const int b = blockIdx.x;
+    float a = 0.f;
+    for (int i = threadIdx.x; i < nss; i += kGemvSsParts) a += ss[(int64_t)b * nss + i];
+    out[b * kGemvSsParts + threadIdx.x] = a;
+}
+
+void launch_ss_fold(const float *ss, int nss, float *out, int B, hipStream_t s) {
+    hipLaunchKernelGGL(k_ss_fold, dim3(B), dim3(kGemvSsParts), 0, s, ss, nss, out);
+}
 
 // One instantiation per (prologue, epilogue) pair the decode step uses.
 // Waves per strip (the K split), from a sweep on MI355X at batch 1: the LM

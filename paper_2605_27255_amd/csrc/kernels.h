@@ -58,6 +58,10 @@ struct GemvParams {
     int krt;                      // k-tiles per range of the k-range kernel (set by launch_gemv)
     int xseg;                     // 2048-column segments per row of the X planes (set by launch_gemv)
 };
+// A prologue that normalises reads up to kGemvSsParts sum-of-squares parts per
+// row (four per lane); launch_ss_fold adds the parts of wider rows to that many.
+constexpr int kGemvSsParts = 256;
+void launch_ss_fold(const float *ss, int nss, float *out, int B, hipStream_t s);   // [B][nss] to [B][kGemvSsParts]
 // Returns 0, or -1 (nothing launched) for a (pro, epi) pair without an
 // instantiation.
 int launch_gemv(const GemvParams &p, int pro, int epi, hipStream_t s);

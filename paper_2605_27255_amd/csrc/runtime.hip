@@ -65,6 +65,7 @@ struct pipo_ctx {
     // decode state and activations
     float *x, *ss_x, *hd, *ss_hd, *logits_b, *logits_d, *apart;
     float *qbuf, *attn_out, *act;
+    float *ss_fold;       // sum-of-squares parts of rows wider than the GEMV prologues read [2][Bmax][kGemvSsParts]
     uint16_t *xh, *xl;    // decode GEMV input planes for larger batches [Bmax][Kmax]
     float *gpart; int64_t gpart_cap;   // decode GEMV k-range partial sums
     int n_cu;             // compute units: workgroups of the batch-1 GEMV
@@ -183,7 +184,17 @@ static void check_launch(pipo_ctx *c, hipStream_t s, int cls, int line) {
 }
 
 // launch_gemv; a (prologue, epilogue) pair it has no kernel for is the call's error
-static void gemv(pipo_ctx *c, const GemvParams &p, int pro, int epi, hipStream_t s) {
+static void gemv(pipo_ctx *c, GemvParams p, int pro, int epi, hipStream_t s) {
+    if (p.nss > kGemvSsParts) {   // hidden above 4096
+        launch_ss_fold(p.ss, p.nss, c->ss_fold, p.B, s);
+        p.ss = c->ss_fold;
+        if (p.ss2) {
+            float *second = c->ss_fold + (int64_t)c->Bmax * kGemvSsParts;
+            launch_ss_fold(p.ss2, p.nss, second, p.B, s);
+            p.ss2 = second;
+        }
+        p.nss = kGemvSsParts;
+    }
     if (launch_gemv(p, pro, epi, s) != 0 && c->enq_rc == PIPO_OK)
         c->enq_rc = fail(c, PIPO_EINVAL, "no decode GEMV kernel for prologue %d with epilogue %d", pro, epi);
 }
@@ -330,6 +341,7 @@ extern "C" int pipo_init_weights(const pipo_config *cfg, uint64_t seed, void *st
         c->hd = a.take<float>((int64_t)B * H);
         c->ss_x = a.take<float>((int64_t)B * (H / 16));
         c->ss_hd = a.take<float>((int64_t)B * (H / 16));
+        c->ss_fold = a.take<float>((int64_t)2 * B * kGemvSsParts);
         c->logits_b = a.take<float>((int64_t)B * V);
         c->logits_d = a.take<float>((int64_t)B * V);
         c->qbuf = a.take<float>((int64_t)B * c->qdim);

@@ -570,6 +570,27 @@ def test_paper_heads_wider_than_the_ffn(torch, hidden, nq, nkv, d, ffn, heads):
     m.close()
 
 
+@pytest.mark.parametrize("hidden", [4096, 4128, 5120, 8192])
+@pytest.mark.parametrize("B,heads", [(1, 0), (3, 7), (20, 0), (43, 7)])
+def test_wide_hidden(torch, hidden, B, heads):
+    """Hidden sizes of 256 sum-of-squares parts per row and of more, through
+    every form of the decode GEMVs and the tiled GEMM: a prefill in two chunks
+    (its last layer runs through the same kernels) and two steps."""
+    cfg = ModelConfig(n_layers=2, hidden=hidden, n_q_heads=4, n_kv_heads=2, head_dim=128, ffn=512, vocab=1008,
+                      rope_base=1e4, heads=heads, gain_mode=1)
+    n, steps = 60, 2
+    prompts = rspec.prompt_tokens(B, n, cfg.vocab, seed=26)
+    m = _model(cfg, seed=18, max_batch=B, max_latent=n // 2 + steps + 1, prefill_chunk=16)
+    W = O.OracleWeights.generate(cfg, seed=18, precision="bf16")
+    # the confidence logit is a dot of hidden values with weights of deviation 0.02: about
+    # 0.02 sqrt(8192) 1.6 = 2.9 at the widest, so that the logits' 5e-3 of it, through a
+    # sigmoid's slope of at most 1/4, is 3.6e-3
+    conf_tol = 1e-3 if hidden <= 5120 else 0.25 * 5e-3 * 2.9
+    rep, _ = run_parity(m, W, prompts, steps, O.Sampling(tau=0.5), log, seqs=sorted({0, B - 1}), conf_tol=conf_tol)
+    rep.check()
+    m.close()
+
+
 # ------------------------------------------------------------ edge cases
 
 def test_tiny_degenerate_and_tile_boundary_prompts(torch):
