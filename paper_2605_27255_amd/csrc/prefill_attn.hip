@@ -94,14 +94,22 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(AttnPrefillParams p) {
             load_to_lds(p.vh + off + u * 512, dst + (KV + u) * 1024, lane16);
         }
     };
-    u32x4 qb[NC][2];   // the query row in fp16, dims 32 c + 16 s + 8 h ..
+    // This lane's query row in fp16, dims 32 c + 16 s + 8 h ..  Rows past the
+    // chunk, and past a shorter prompt's positions, hold what an earlier call
+    // left: they take zeros, whose scores never move a running maximum, so that
+    // they have no say in the rescaling of the rows beside them.
+    u32x4 qb[NC][2];
     {
-        const int row = min(q0 + j, p.g.mpad - 1);           // rows past the chunk are never written
-        const uint16_t *q = p.q + (((int64_t)b * p.n_q + head) * p.g.mpad + row) * D + 8 * h;
+        const int nrow = p.g.ntok ? min(p.g.clen, seq_positions(p.g, b) - p.g.c0) : p.g.clen;
+        const bool own = q0 + j < nrow;
+        const uint16_t *q = p.q + (((int64_t)b * p.n_q + head) * p.g.mpad + min(q0 + j, nrow - 1)) * D + 8 * h;
 #pragma unroll
         for (int c = 0; c < NC; ++c)
 #pragma unroll
-            for (int s = 0; s < 2; ++s) qb[c][s] = *(const u32x4 *)(q + 32 * c + 16 * s);
+            for (int s = 0; s < 2; ++s) {
+                const u32x4 v = *(const u32x4 *)(q + 32 * c + 16 * s);
+                qb[c][s] = own ? v : u32x4{0u, 0u, 0u, 0u};
+            }
     }
     issue(0, 0);
 
