@@ -525,7 +525,13 @@ __global__ __launch_bounds__(kSampThreads) void k_sample(SampleParams p) {
 // whole-row selection over the listed candidates (about nseg k of them, in
 // LDS), with the same arithmetic, so the same token.  Should the ties of a
 // segment not fit its list, the row is selected from the logits as before.
+// The two launches pay where the whole-row kernel takes a fourth 4096-id step a
+// pass (a fifth with more than 16 sequences).  One step of a tiny model, two
+// calls, top-k 20, in us, whole row -> lists: 4096 ids and 8 sequences 131 -> 161,
+// 12288 165 -> 170, 12304 171 -> 170, 24576 210 -> 179, 50640 311 -> 208; 12304
+// and 48 sequences 205 -> 214, 16384 212 -> 218, 16400 222 -> 217, 24576 245 -> 226.
 constexpr int kListMax = kSampCandidates;    // candidates of a row
+static bool list_pays(int V, int B) { return V > (B <= 16 ? 12288 : 16384); }
 
 template <int NTH>
 __global__ __launch_bounds__(NTH) void k_sample_cand(SampleParams p) {
@@ -892,7 +898,7 @@ int sample_segments(int B) {
 }
 
 void launch_sample(const SampleParams &p, hipStream_t s) {
-    if (p.cand_val && p.top_k > 0 && p.top_k < p.V && p.top_k <= kListMax / p.nseg) {
+    if (p.cand_val && list_pays(p.V, p.B) && p.top_k > 0 && p.top_k < p.V && p.top_k <= kListMax / p.nseg) {
         // segments of whole sub-tiles per wave; sixteen waves where a segment is long
         SampleParams q = p;
         const int per = (p.V + p.nseg - 1) / p.nseg, unit = per > 8192 ? 4096 : 1024;

@@ -15,9 +15,10 @@ from oracle import pipo_oracle as O
 pytestmark = pytest.mark.gpu
 
 
-# vocabularies of one, a few and many segments (ends of segments, sub-tiles and
-# rows), top-k of one, within and past a segment's list
-@pytest.mark.parametrize("V", [16, 1008, 4096, 33024, 151936])
+# vocabularies on both sides of the sizes from which rows are split (12304 ids up to
+# 16 sequences, 16400 with more; ends of segments, sub-tiles and rows), top-k of one,
+# within and past a segment's list
+@pytest.mark.parametrize("V", [16, 1008, 4096, 12288, 12304, 16384, 16400, 33024, 151936])
 @pytest.mark.parametrize("B,top_k", [(1, 1), (3, 20), (3, 64), (3, 65), (20, 20), (64, 200), (64, 512)])
 def test_eval_sampler_split_rows(V, B, top_k):
     import torch
