@@ -325,7 +325,9 @@ extern "C" int pipo_init_weights(const pipo_config *cfg, uint64_t seed, void *st
 
     // ---- KV cache, RoPE table, activations ------------------------------
     Arena a;
-    const int64_t mcap = (int64_t)B * round_up(c->chunk, 64);   // rows per chunk
+    const int64_t mcap = (int64_t)B * round_up(std::min(c->chunk, cfg->max_latent), 64);   // rows per chunk
+    // (the last layer, or the MTP layer after it, runs no prefill attention)
+    const bool prefill_attn = c->L > (c->heads & PIPO_HEADS_MTP_LAYER ? 0 : 1);
     const int S_att = 64;
     for (int pass = 0; pass < 2; ++pass) {
         a.used = 0;
@@ -387,8 +389,8 @@ extern "C" int pipo_init_weights(const pipo_config *cfg, uint64_t seed, void *st
         c->p_xn = a.take<uint16_t>(mcap * H);
         c->p_xn_lo = a.take<uint16_t>(mcap * H);
         c->p_q = a.take<uint16_t>(mcap * c->qdim);
-        c->p_kh = a.take<uint16_t>((int64_t)B * c->kv_bstride);
-        c->p_vh = a.take<uint16_t>((int64_t)B * c->kv_bstride);
+        c->p_kh = a.take<uint16_t>(prefill_attn ? (int64_t)B * c->kv_bstride : 0);
+        c->p_vh = a.take<uint16_t>(prefill_attn ? (int64_t)B * c->kv_bstride : 0);
         c->p_o = a.take<uint16_t>(mcap * c->qdim);
         c->p_o_lo = a.take<uint16_t>(mcap * c->qdim);
         // ... and, of a chunk, the compressor's H-wide rows and the MTP projection's 2H-wide inputs
