@@ -143,8 +143,9 @@ __device__ __forceinline__ void gemm_epi(const GemmParams &p, f32x4 a, f32x4 c, 
     }
 }
 
-// A decode step's RMSNorm scale of row m from its sum-of-squares parts: lane
-// (m, half h) adds its half of them in order, then the halves.
+// A decode step's RMSNorm scale of row m from its sum-of-squares parts (hidden /
+// 16 of them, an even number): lane (m, half h) adds its half of them in order,
+// then the halves.
 template <int EPI>
 __device__ __forceinline__ float norm_scale(const GemmParams &p, int m) {
     if (!(EPI == EPI_QKV || EPI == EPI_SWIGLU) || !p.ss_in) return 1.f;
@@ -160,7 +161,6 @@ __device__ __forceinline__ float norm_scale(const GemmParams &p, int m) {
     } else {
 #pragma unroll 8
         for (int i = 0; i < half; ++i) s += q[i];
-        if ((p.nss & 1) && h) s += q[half];
     }
     s += __shfl_xor(s, 32);
     return rsqrtf(s / (float)p.K + p.eps);
@@ -390,17 +390,23 @@ using TileT = GemmTile<1, 1, 4, 1, 4, 4>;   // 128 x 32, 48 KB (four stages)
 // it is given at a measured cost per 32-wide k step and tile (us; a quarter
 // more while it holds one workgroup only): whole rounds of 256 tiles plus the
 // rest, cut into ksplit ranges over the CUs, plus the finishing launch and the
-// traffic of the partial sums.  Measured on MI355X (us; the 16x16x32 kernel
-// with W straight to registers that this one replaced -> the choice here):
+// traffic of the partial sums.  Measured inside whole prefills on MI355X (us,
+// finishing launch included; the 16x16x32 kernel with W straight to registers
+// that this one replaced -> the choice here):
 //   rows x K, tokens            before     now
-//   19456 x 2560, 4096          712        605 (256 x 128, the last half round in two ranges)
-//    6144 x 2560, 4096          236        219 (256 x 128)
-//    2560 x 9728, 4096          316        321 (256 x 128, the last quarter round in two)
-//    2560 x 9728, 1024          143        100 (256 x 128 in three ranges)
-//    2560 x 9728, 128           131         23 (128 x 64 in six to twelve)
-//   19456 x 2560, 32             39         18 (128 x 32)
-// At 4096 tokens the larger matrices run at 1.15-1.35 PFLOP/s (hi and lo plane
-// counted), the rate a large library product reaches on this card (1.32).
+//   19456 x 2560, 4096          625        610 (256 x 128, the last half round in two ranges)
+//    6144 x 2560, 4096          239        223 (256 x 128)
+//    2560 x 9728, 4096          324        341 (256 x 128, the last quarter round in four)
+//    2560 x 4096, 4096          147        163 (the same)
+//    2560 x 9728, 2048          191        190 (256 x 128 in three ranges)
+//    2560 x 4096, 2048           89         92 (128 x 64, the last half round in two)
+//    2560 x 9728, 1024          150        117 (128 x 64, the last quarter round in four)
+//   19456 x 2560, 128            53         41 (128 x 64, 48 tiles past a round in five)
+//    2560 x 9728, 128           162         25 (128 x 64 in six)
+//   19456 x 2560, 64             53         34 (128 x 64)
+//   19456 x 2560, 32             51         27 (128 x 32 in three)
+// At 4096 tokens the matrices run at 1.06-1.34 PFLOP/s (hi and lo plane counted);
+// a large library product reaches 1.32 on this card.
 struct GemmPlan {
     int shape, full, ksplit;
 };

@@ -540,10 +540,15 @@ static AttnDecodeParams attn_params(const pipo_ctx *c, uint16_t *kc, uint16_t *v
 // (prefill_gemm.hip) instead of the decode GEMVs: past 16 the GEMVs stage two
 // or more column tiles of X per workgroup and cut K into ranges to do so,
 // while the tiled GEMM takes X from planes that the producing kernels write.
-// Four layers of the 4B (9B) width over 256 latents, one pair step in us,
-// GEMVs -> tiled GEMM: 24 sequences 480 -> 494 (652 -> 683), 32: 503 -> 515
-// (681 -> 699), 40: 598 -> 590 (795 -> 821), 48: 616 -> 603 (847 -> 837),
-// 64: 739 -> 648 (982 -> 900).
+// Four layers over 256 latents with a small vocabulary, one pair step in us,
+// GEMVs -> tiled GEMM, at 41, 48, 49 (four column tiles) and 64 sequences:
+//   hidden  256:  272 -> 194   277 -> 194   310 -> 205   318 -> 207
+//   hidden 1024:  385 -> 294   392 -> 299   441 -> 309   459 -> 320
+//   hidden 2560:  582 -> 543   597 -> 544   676 -> 562   717 -> 581
+//   hidden 4096:  785 -> 723   827 -> 729   939 -> 767   962 -> 789
+// At 33 to 40 (three column tiles) the tiled GEMM measures faster too (hidden
+// 2560 at 40: 579 -> 537), at 18 to 32 between 12% faster and 5% slower by
+// width; those keep the GEMVs, whose sums the results there have always had.
 constexpr int kTiledMinBatch = 41;
 
 // One decoder layer at the current positions, its matrices through the tiled
@@ -1140,9 +1145,10 @@ extern "C" int pipo_decode_step(pipo_ctx *c, const int32_t *d_in_pairs, pipo_pai
 }
 
 // The pair step of pipo_decode_step, launched eagerly on the caller's stream
-// with the attention and k-range partials in the device's static scratch:
-// no allocation and no graph instantiation, so a caller under HIP graph
-// capture can record it.
+// with the attention partials and the GEMVs' k-range partials in the device's
+// static scratch (the tiled GEMM's, from kTiledMinBatch sequences on, are in the
+// context's own workspace): no allocation and no graph instantiation, so a
+// caller under HIP graph capture can record it.
 extern "C" int pipo_decode_step_noalloc(pipo_ctx *c, const int32_t *d_in_pairs, pipo_pair *d_out,
                                         float *d_logits_b, float *d_logits_d, void *stream) {
     if (!c) return fail(nullptr, PIPO_EINVAL, "ctx is NULL");

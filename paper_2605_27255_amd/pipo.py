@@ -183,7 +183,8 @@ class PipoModel:
 
     def decode_step_noalloc(self, out, in_pairs=None, logits_b=None, logits_d=None):
         """pipo_decode_step_noalloc into caller-provided tensors: the library
-        allocates nothing and builds no graph (scratch in its static array)."""
+        allocates nothing and builds no graph (scratch in its static array and
+        the context's workspaces)."""
         self._check(self.lib.pipo_decode_step_noalloc(self.ctx, _ptr(in_pairs), _ptr(out), _ptr(logits_b),
                                                       _ptr(logits_d), self._stream()))
 

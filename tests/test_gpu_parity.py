@@ -203,10 +203,10 @@ def test_head_dim_64_attention_finishes_qkv(torch, hidden, nq, nkv):
 @pytest.mark.parametrize("hidden,nq,nkv,d,B", [(2560, 32, 8, 128, 64), (2048, 32, 8, 64, 32)])
 def test_workgroup_merged_attention_unfused(torch, hidden, nq, nkv, d, B):
     """Batch x KV groups >= 256, so the decode attention runs one workgroup per
-    (sequence, KV group) and merges its splits (one per wave) in LDS, with the QKV
-    GEMV finishing its own k-ranges (five ranges at 4B width and batch 64,
-    eight at head dim 64 and batch 32): the unfused form of that kernel, at
-    d = 128 and 64.  The oracle replays the first and the last sequence."""
+    (sequence, KV group) and merges its splits (one per wave) in LDS, with QKV
+    finished before it: by the tiled GEMM at 4B width and batch 64 (d = 128, output
+    as planes), by the GEMV's own finish of eight k-ranges at head dim 64 and
+    batch 32 (fp32 output).  The oracle replays the first and the last sequence."""
     cfg = ModelConfig(n_layers=1, hidden=hidden, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, ffn=2048, vocab=4096,
                       rope_base=1e4)
     n, steps = 96, 3
@@ -845,8 +845,9 @@ def test_tiny_batch64_ragged_eval_sampler(torch):
 
 
 def test_4b_width_batch64_top_p(torch):
-    """4B width, two layers, 64 sequences: the k-range and wide GEMV forms at
-    four column tiles, T 0.6, top-p 0.95, tau 0.7."""
+    """4B width, two layers, 64 sequences: the layers through the tiled GEMM, the
+    heads through the k-range and wide GEMV forms at four column tiles, T 0.6,
+    top-p 0.95, tau 0.7."""
     cfg = DENSE_4B.with_layers(2)
     B, n, steps = 64, 48, 2
     prompts = rspec.prompt_tokens(B, n, cfg.vocab, seed=61)

@@ -62,8 +62,8 @@ def test_noalloc_step_matches_decode_step_two_calls(torch):
 
 
 def test_noalloc_step_refuses_attention_partials_past_the_scratch(torch):
-    """Attention partials of 64 x 1024 heads x (64 + 2) floats (17.3 MB) do not
-    fit the 16 MiB scratch: PIPO_ECAPACITY, and the context still steps
+    """Attention partials of 64 x 1024 heads x 4 splits x (64 + 32) floats (101 MB) do
+    not fit the 16 MiB scratch: PIPO_ECAPACITY, and the context still steps
     through pipo_decode_step."""
     from paper_2605_27255_amd import PipoError, PIPO_ECAPACITY
     cfg = ModelConfig(n_layers=1, hidden=256, n_q_heads=1024, n_kv_heads=64, head_dim=64, ffn=256, vocab=4096,
