@@ -283,6 +283,25 @@ def regular_leg(wl, prompts, seeds, pipo_ttft, pipo_ms_step, acc_rate, pipo_job_
     return res
 
 
+def prefill_gemm_flops(m, rows):
+    """(useful, issued) flops of the prefill GEMMs over ``rows`` latents in all: two per
+    weight and latent, of the layer that runs last the keys and values only (the last
+    backbone layer, or the MTP layer after all of them); every GEMM but the one on
+    the gathered embeddings also multiplies the activations' lo plane."""
+    h, f, L = m.hidden, m.ffn, m.n_layers
+    layer = (m.q_dim + 2 * m.kv_dim) * h + h * m.q_dim + 3 * f * h
+    mtp = bool(m.heads & HEADS_MTP_LAYER)
+    full = L if mtp else max(L - 1, 0)
+    deep = full * layer + (2 * m.kv_dim * h if mtp or L else 0)
+    deep += 2 * h * h if mtp else 0                                # W_fc
+    deep += h * h if m.heads & HEADS_MLP_COMPRESSOR else 0         # W2
+    return 2.0 * rows * (deep + 2 * h * h), 2.0 * rows * (2 * deep + 2 * h * h)
+
+
+# sequences from which the decoder layers' matrices go through the tiled GEMM
+TILED_MIN_BATCH = 41
+
+
 def measure(wl, n_steps, n_warmup, profile=True, ragged=False):
     """Time ``n_steps`` whole requests of workload ``wl`` after ``n_warmup``
     untimed ones (prompts resident in HBM), then, with ``profile``, one eager
@@ -399,12 +418,17 @@ def measure(wl, n_steps, n_warmup, profile=True, ragged=False):
         res["roofline"] = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                            "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                            "traffic": measured_traffic(wl.name),
-                           "kernel": "k_gemv (decode weight-streaming GEMM, all launches of a pair step)",
+                           "kernel": ("k_gemv (decode weight-streaming GEMM, all launches of a pair step)"
+                                      if B < TILED_MIN_BATCH else
+                                      "k_gemm (decoder layers) and k_gemv (heads), all launches of a pair step"),
                            "bytes_per_launch": round(gb / gemv_n), "launches_per_step": gemv_n,
                            "avg_launch_us": round(gemv_ms / gemv_n * 1e3, 3),
-                           "timing": "HIP events recorded by each k_gemv launch itself "
-                                     "(hipExtLaunchKernelGGL start/stop) on the library stream, in an "
-                                     "eager profiling pass after the timed region"}
+                           "timing": ("HIP events recorded by each k_gemv launch itself "
+                                      "(hipExtLaunchKernelGGL start/stop) on the library stream, in an "
+                                      "eager profiling pass after the timed region"
+                                      if B < TILED_MIN_BATCH else
+                                      "HIP events around each matrix's launches on the library stream, in an "
+                                      "eager profiling pass after the timed region")}
         if prof.get("attn_decode", (0, 0))[1]:
             att_ms = prof["attn_decode"][0] / psteps
             res["attn_decode"] = {"ms_per_pair_step": round(att_ms, 4), "kv_gb_per_step": round(kv_mean / 1e9, 4),
@@ -413,15 +437,7 @@ def measure(wl, n_steps, n_warmup, profile=True, ragged=False):
         res["kernel_ms_per_pair_step"] = per_class
         res["prefill_kernel_ms"] = {k: round(v[0], 3) for k, v in pre.items() if v[1]}
         if pre.get("prefill_gemm", (0, 0))[1]:
-            # the prefill GEMMs (k_gemm): 2 flops per weight per latent row (of the last
-            # layer the keys and values only); every layer GEMM also multiplies the
-            # activations' lo plane (a second MFMA)
-            h, f, L = m.hidden, m.ffn, m.n_layers
-            layer_w = (m.q_dim + 2 * m.kv_dim) * h + h * m.q_dim + 2 * f * h + h * f
-            rows = B * wl.latents
-            deep_w = (L - 1) * layer_w + 2 * m.kv_dim * h
-            useful = 2.0 * rows * (deep_w + 2 * h * h)
-            issued = 2.0 * rows * (2 * deep_w + 2 * h * h)
+            useful, issued = prefill_gemm_flops(m, sum(lat))
             sec = pre["prefill_gemm"][0] * 1e-3
             res["prefill_gemm"] = {
                 "kernel": "k_gemm", "bound": "mfma", "peak_tflops": 2500.0,

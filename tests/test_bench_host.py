@@ -34,3 +34,18 @@ def test_workloads_have_the_stated_shapes(name):
     wl = WORKLOADS[name]
     assert wl.latents == (wl.prompt_tokens + 1) // 2
     assert wl.model.vocab % 16 == 0 and wl.model.hidden % 32 == 0
+
+
+def test_prefill_gemm_flops_by_layer_and_head():
+    import bench
+    from synth.configs import HEADS_PAPER, ModelConfig
+    kw = dict(n_layers=3, hidden=64, n_q_heads=4, n_kv_heads=2, head_dim=64, ffn=96, vocab=64)
+    qkv, o, ffn, kv = (256 + 2 * 128) * 64, 64 * 256, 3 * 64 * 96, 2 * 128 * 64
+    emb = 2 * 64 * 64                                          # the GEMM on the embeddings: one plane
+    useful, issued = bench.prefill_gemm_flops(ModelConfig(**kw), 10)
+    deep = 2 * (qkv + o + ffn) + kv
+    assert (useful, issued) == (20.0 * (deep + emb), 20.0 * (2 * deep + emb))
+    # the App. B heads: every backbone layer, W2, W_fc and the MTP layer's keys and values
+    useful, issued = bench.prefill_gemm_flops(ModelConfig(**kw, heads=HEADS_PAPER), 10)
+    deep = 3 * (qkv + o + ffn) + 64 * 64 + 2 * 64 * 64 + kv
+    assert (useful, issued) == (20.0 * (deep + emb), 20.0 * (2 * deep + emb))
