@@ -770,14 +770,19 @@ static bool writable_here(const pipo_ctx *c, void *p, size_t bytes, size_t align
     return at.type == hipMemoryTypeDevice && at.device == c->dev && (size_t)((char *)p - (char *)base) + bytes <= size;
 }
 
+static bool apart(const void *a, size_t na, const void *b, size_t nb) {
+    return !a || !b || (const char *)a + na <= (const char *)b || (const char *)b + nb <= (const char *)a;
+}
+
 // A step's results into the caller's buffers: one launch (a copy each cost
 // about 2 us of a step), or copies where a kernel cannot write there (which
-// refuse a buffer that ends too early).
+// refuse a buffer that ends too early) or buffers overlap (the later copy wins).
 static int copy_results(pipo_ctx *c, void *d0, const void *s0, int bytes, float *d_lb, float *d_ld, hipStream_t s) {
     const int64_t n = (int64_t)c->batch * c->V;
     const size_t lbytes = sizeof(float) * (size_t)n;
     if (writable_here(c, d0, bytes, 4) && (!d_lb || writable_here(c, d_lb, lbytes, 16)) &&
-        (!d_ld || writable_here(c, d_ld, lbytes, 16))) {
+        (!d_ld || writable_here(c, d_ld, lbytes, 16)) && apart(d0, bytes, d_lb, lbytes) && apart(d0, bytes, d_ld, lbytes) &&
+        apart(d_lb, lbytes, d_ld, lbytes)) {
         launch_copy_out(d0, s0, bytes / 4, d_lb, c->logits_b, d_lb ? n : 0, d_ld, c->logits_d, d_ld ? n : 0, s);
         HIP_TRY(c, hipGetLastError());
         return PIPO_OK;

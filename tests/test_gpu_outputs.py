@@ -49,6 +49,21 @@ def test_outputs_at_any_alignment(models, off, noalloc):
         assert (b[:off] == 7).all() and (b[off + n:] == 7).all()
 
 
+@pytest.mark.parametrize("shift", [0, 4, 16, 4096])
+def test_overlapping_outputs_are_written_in_order(models, shift):
+    """The draft logits over the backbone's, from `shift` values on: the pairs, then
+    the backbone logits, then the draft logits, as separate copies leave them."""
+    import torch
+    ref, m = models
+    n = 2 * TINY.vocab
+    w_out, w_lb, w_ld = ref.decode_step(logits=True)
+    buf = torch.full((n + shift,), 7.0, device="cuda")
+    out = torch.empty((2, 4), dtype=torch.int32, device="cuda")
+    m.decode_into(out, logits_b=buf[:n], logits_d=buf[shift:])
+    want = torch.cat([w_lb.flatten()[:shift], w_ld.flatten()])
+    _check((w_out, want), (out, buf))
+
+
 def test_outputs_in_pinned_host_memory(models):
     import torch
     ref, m = models
