@@ -547,8 +547,8 @@ static AttnDecodeParams attn_params(const pipo_ctx *c, uint16_t *kc, uint16_t *v
 //   hidden 2560:  582 -> 543   597 -> 544   676 -> 562   717 -> 581
 //   hidden 4096:  785 -> 723   827 -> 729   939 -> 767   962 -> 789
 // At 33 to 40 (three column tiles) the tiled GEMM measures faster too (hidden
-// 2560 at 40: 579 -> 537), at 18 to 32 between 12% faster and 5% slower by
-// width; those keep the GEMVs, whose sums the results there have always had.
+// 2560 at 40: 579 -> 537) and at 18 to 32 between 12% faster and 5% slower by
+// width, so the line could lie lower; it is where every width gains.
 constexpr int kTiledMinBatch = 41;
 
 // One decoder layer at the current positions, its matrices through the tiled
