@@ -770,7 +770,7 @@ static bool writable_here(const pipo_ctx *c, void *p, size_t bytes, size_t align
     return at.type == hipMemoryTypeDevice && at.device == c->dev && (size_t)((char *)p - (char *)base) + bytes <= size;
 }
 
-static bool apart(const void *a, size_t na, const void *b, size_t nb) {
+static bool disjoint(const void *a, size_t na, const void *b, size_t nb) {
     return !a || !b || (const char *)a + na <= (const char *)b || (const char *)b + nb <= (const char *)a;
 }
 
@@ -781,8 +781,8 @@ static int copy_results(pipo_ctx *c, void *d0, const void *s0, int bytes, float 
     const int64_t n = (int64_t)c->batch * c->V;
     const size_t lbytes = sizeof(float) * (size_t)n;
     if (writable_here(c, d0, bytes, 4) && (!d_lb || writable_here(c, d_lb, lbytes, 16)) &&
-        (!d_ld || writable_here(c, d_ld, lbytes, 16)) && apart(d0, bytes, d_lb, lbytes) && apart(d0, bytes, d_ld, lbytes) &&
-        apart(d_lb, lbytes, d_ld, lbytes)) {
+        (!d_ld || writable_here(c, d_ld, lbytes, 16)) && disjoint(d0, bytes, d_lb, lbytes) && disjoint(d0, bytes, d_ld, lbytes) &&
+        disjoint(d_lb, lbytes, d_ld, lbytes)) {
         launch_copy_out(d0, s0, bytes / 4, d_lb, c->logits_b, d_lb ? n : 0, d_ld, c->logits_d, d_ld ? n : 0, s);
         HIP_TRY(c, hipGetLastError());
         return PIPO_OK;

@@ -101,7 +101,7 @@ def test_batched_regular_steps_against_the_oracle():
     m.close()
 
 
-# one and two KV groups: 4 to 16 splits, merged on their XCD or by the merge launch
+# one and two KV groups: 6 to 16 splits, merged on their XCD or by the merge launch
 @pytest.mark.parametrize("nq,nkv,d,B", [(16, 1, 64, 41), (4, 2, 128, 48), (12, 2, 64, 64), (3, 1, 128, 64)])
 @pytest.mark.parametrize("xcd", [True, False])
 def test_batched_attention_splits(monkeypatch, nq, nkv, d, B, xcd):
